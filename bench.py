@@ -122,7 +122,7 @@ def main():
         torch.cuda.synchronize()
         del xa, ya
 
-    # warmup; the matrix-product sites over the neighbour slots are timed one
+    # warmup; the attention's kernels are timed one
     # warmup step each to pick the dominant one
     site_ms = {}
     for i in range(args.warmup):
@@ -185,13 +185,12 @@ def main():
                    "n_heads": w.n_heads, "first_batch": b0, "order": "lag-1"},
     }
 
-    # algorithmic work of the dominant kernel: valid neighbour slots of the steps it was timed on
+    # algorithmic work of the dominant kernel on the steps it was timed on (one launch covers a step's queries)
     lo2, hi2 = args.warmup + args.steps, n_steps
     valid_pairs = sum(valid_slots(runner, s, w, b0 + i) for i in range(lo2, hi2))
     launches_per_step = dom_launches / args.steps
-    # every launch of a hot site covers all valid slots of its step (K and V share one launch)
-    per_launch_pairs = valid_pairs / args.steps / max(launches_per_step, 1.0)
-    flops = 2.0 * per_launch_pairs * SITE_K(dominant, w) * SITE_N(dominant, w)
+    flops = site_flops(dominant, w, valid_pairs / args.steps, 3 * sum(n_tar[lo2:hi2]) / args.steps)
+    flops /= max(launches_per_step, 1.0)
     avg_s = dom_ms / 1e3 / max(dom_launches, 1)
     peak = BF16_PEAK_TFLOPS if w.dtype == "bf16" else FP32_PEAK_TFLOPS
     achieved = flops / avg_s / 1e12
@@ -264,18 +263,20 @@ def other_model(args):
     print(json.dumps(out), flush=True)
 
 
-# Matrix-product call sites over the neighbour slots (the largest products of the step).
-HOT_SITES = ("gemm_kv_proj", "gemm_kv_dw", "gemm_kv_dx")
+# The attention's kernels (the largest of the step): forward, data gradients, weight gradients.
+HOT_SITES = ("attn_fwd", "attn_bwd", "attn_dw")
 
 
-def SITE_K(site, w):
-    """Reduction length per neighbour slot of each hot site's product."""
-    return {"gemm_kv_proj": w.d_kv, "gemm_kv_dw": 2 * w.d_attn, "gemm_kv_dx": 2 * w.d_attn}[site]
-
-
-def SITE_N(site, w):
-    """Output width: K|V (2 d_attn), [dW_k; dW_v] (d_kv per row of 2 d_attn), dphi (d_time)."""
-    return {"gemm_kv_proj": 2 * w.d_attn, "gemm_kv_dw": w.d_kv, "gemm_kv_dx": w.d_time}[site]
+def site_flops(site, w, slots, queries):
+    """Operations of one launch over `queries` query rows and their `slots` valid neighbour slots: the
+    products per query (the key/value weights meet one projected vector per query and head) and the
+    dot-length passes per slot."""
+    a, m, kv, t = w.d_attn, w.d_mem, w.d_kv, w.d_time
+    per_q = {"attn_fwd": a * m + 2 * a * kv + 2 * a * a + a * (a + m),
+             "attn_bwd": a * m + 3 * a * kv + 2 * a * a + a * (a + m),
+             "attn_dw": a * m + 2 * a * kv + 2 * a * a + a * (a + m)}[site]
+    per_slot = {"attn_fwd": 2 * kv, "attn_bwd": 2 * kv + 2 * (m + t), "attn_dw": 0}[site]
+    return 2.0 * (queries * per_q + slots * w.n_heads * per_slot)
 
 
 def valid_slots(runner, s, w, b):
@@ -303,7 +304,7 @@ def valid_slots(runner, s, w, b):
 CSRC = os.path.join(ROOT, "paper_2608_16305_amd", "csrc")
 # sources that define the hot-site kernels and their launches
 TRAFFIC_SOURCES = ("common.h", "gemm.h", "gemm.hip", "gemm_nt.hip", "gemm_nn.hip", "gemm_tn.hip", "gemm_rs.h",
-                   "gemm_rs.hip", "lds_dma.h", "attention.hip")
+                   "gemm_rs.hip", "lds_dma.h", "attention.hip", "attn_proj.h", "attn_proj.hip")
 
 
 def kernel_fingerprint():
@@ -333,8 +334,8 @@ def read_traffic(site, w):
 
 
 def _site_of(name):
-    for site, tag in (("gemm_kv_proj", "KvProj"), ("gemm_kv_dw", "KvDw"), ("gemm_kv_dx", "KvDx")):
-        if f"site::{tag}," in name:
+    for site, tag in (("attn_fwd", "k_proj_fwd<"), ("attn_bwd", "k_proj_bwd<"), ("attn_dw", "k_proj_dw(")):
+        if tag in name:
             return site
     return None
 
@@ -383,7 +384,7 @@ def write_traffic(args):
         json.dump(rec, fh, indent=1)
         fh.write("\n")
     n, mib = args.workload, args.copy_probe
-    lines = [f"# HBM traffic of the neighbour-slot products on {w.name} (fp32)", "",
+    lines = [f"# HBM traffic of the attention's kernels on {w.name} (fp32)", "",
              "Two counter passes, each its own run (repository root, MI355X), then the record:", "", "```",
              f"timeout -s KILL 400 rocprofv3 --pmc FETCH_SIZE -f csv -d gpurun_out/pmcF_w{n} -o run -- python -u bench.py "
              f"--workload {n} --steps 2 --warmup 1 --cpu-steps 0 --copy-probe {mib}",
@@ -589,7 +590,7 @@ def step_report(args):
              f"{sum(c for _, c in per.values()) / ns:.0f} launches (two streams overlap, so the step takes less).", "",
              f"bench.py headline (separate run, `python -u bench.py --workload {n} --cpu-steps 0`): "
              f"{bench['value'] / 1e6:.3f} M events/s, {bench['ms_per_step'] * 1e3:.1f} us per step; step sizes "
-             f"{json.dumps(bench.get('step_counts', {}))}; dominant product `{rl['kernel']}` "
+             f"{json.dumps(bench.get('step_counts', {}))}; dominant kernel `{rl['kernel']}` "
              f"{rl['avg_launch_us']:.1f} us per launch, {rl['achieved']:.1f} TFLOP/s = {100 * rl['frac']:.2f}% of "
              f"{rl['peak']} TFLOP/s.", "",
              "| % of kernel time | us/step | launches/step | us/launch | kernel |", "|---|---|---|---|---|"]

@@ -15,6 +15,7 @@
 // The projections run on the MFMA strip GEMM; gathers, per-query softmax and
 // weighted sums are wave-per-query kernels.
 #include "gemm.h"
+#include "attn_proj.h"
 #include "ops.h"
 
 namespace mtgnn {
@@ -764,6 +765,42 @@ __global__ void k_occ_keys(const int32_t* __restrict__ q_node, const int32_t* __
   }
 }
 
+// The same over the slots where they are sampled: occurrence max_q + q k + j is slot j of query q, valid
+// if j is among the query's leading valid neighbours.  Blocks below `qblocks` take 256 queries' own
+// occurrences, the others the slots of 256 / k queries, whose neighbours they share through LDS.
+__global__ __launch_bounds__(256) void k_occ_keys_grid(const int32_t* __restrict__ q_node,
+                                                       const int32_t* __restrict__ nbr,
+                                                       const int32_t* __restrict__ n_q, int64_t max_q, int k,
+                                                       int64_t qblocks, const int32_t* __restrict__ uniq,
+                                                       const int32_t* __restrict__ n_rows, int64_t max_rows,
+                                                       const int32_t* __restrict__ row_of, uint32_t sentinel,
+                                                       uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+  __shared__ int32_t s_nb[256];
+  const int32_t rows = (int32_t)eff_count(max_rows, n_rows);
+  const int64_t Q = eff_count(max_q, n_q);
+  if ((int64_t)blockIdx.x < qblocks) {
+    const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (o >= max_q) return;
+    keys[o] = occ_key(o < Q ? q_node[o] : -1, uniq, rows, row_of, sentinel);
+    vals[o] = (uint32_t)o;
+    return;
+  }
+  const int per = 256 / k;   // queries per block
+  const int64_t q0 = ((int64_t)blockIdx.x - qblocks) * per;
+  const int t = threadIdx.x, j = t % k;
+  const int64_t q = q0 + t / k;
+  const bool in = t < per * k && q < max_q;
+  int32_t node = in && q < Q ? nbr[q * k + j] : -1;
+  s_nb[t] = node;
+  __syncthreads();
+  if (!in) return;
+  for (int i = t - j; node >= 0 && i < t; ++i)
+    if (s_nb[i] < 0) node = -1;
+  const int64_t o = max_q + q * k + j;
+  keys[o] = occ_key(node, uniq, rows, row_of, sentinel);
+  vals[o] = (uint32_t)o;
+}
+
 // seg_lo[row], seg_hi[row]: the sorted positions [lo, hi) holding row's occurrences.
 __global__ void k_seg_bounds(const uint32_t* __restrict__ keys, int64_t n, uint32_t sentinel,
                              int32_t* __restrict__ seg_lo, int32_t* __restrict__ seg_hi) {
@@ -786,7 +823,8 @@ struct SegCtx {
   int64_t max_q;
   const float* dhq;   // [Q, ldq] query-side gradient of M[q] (columns [0, dm))
   int64_t ldq;
-  const float* dkv;   // [P, 2 da] compact-slot gradient of (K, V)
+  const float* dkv;   // [P, 2 da] compact-slot gradient of (K, V), or null
+  const float* dx;    // dkv null: [P, dm] the slots' row gradients themselves (w2 = 0)
   int dm, w2;         // w2 = 2 da ; row width W = dm + w2
   float* S;           // [rows, W] complete sums (columns [0, dm) go to D instead)
   float* D;           // [rows, dm] d M' itself: the dh_q sums land there, the dK|dV product adds to them
@@ -815,6 +853,13 @@ __device__ __forceinline__ void seg_row_nc(const SegCtx& c, uint32_t o, float* r
   const int W = c.dm + c.w2;
   if ((int64_t)o < c.max_q) {
     const float* src = c.dhq + (int64_t)o * c.ldq;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int col = lane + 64 * i;
+      r[i] = col < c.dm ? src[col] : 0.f;
+    }
+  } else if (c.dx) {
+    const float* src = c.dx + ((int64_t)o - c.max_q) * c.dm;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int col = lane + 64 * i;
@@ -962,9 +1007,11 @@ __global__ __launch_bounds__(256) void k_segsum_tiles_v4(SegCtx c) {
       const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)my_key, p < cnt ? p : 0);
       const bool live = p < cnt && k != c.sentinel;
       const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)my_val, live ? p : 0);
-      const bool isq = (int64_t)o < c.max_q;
-      const float* src = isq ? c.dhq + (int64_t)o * c.ldq : c.dkv + ((int64_t)o - c.max_q) * c.w2 - c.dm;
-      const int lo = isq ? 0 : dm4, hi = isq ? dm4 : W4;   // the row's groups: [lo, hi), never empty
+      const bool isq = (int64_t)o < c.max_q, whole = isq || c.dx;
+      const float* src = isq     ? c.dhq + (int64_t)o * c.ldq
+                         : c.dx ? c.dx + ((int64_t)o - c.max_q) * c.dm
+                                : c.dkv + ((int64_t)o - c.max_q) * c.w2 - c.dm;
+      const int lo = whole ? 0 : dm4, hi = whole ? dm4 : W4;   // the row's groups: [lo, hi), never empty
       ra[u] = *(const f32x4*)(src + 4 * min(max(qa, lo), hi - 1));
       rb[u] = *(const f32x4*)(src + 4 * min(max(qb, lo), hi - 1));
       va[u] = live && qa >= lo && qa < hi;
@@ -1243,6 +1290,7 @@ struct BwdWs {
   size_t scratch_bytes;
   char* sort_scratch;     // radix sort of the dM' grouping (disjoint: the two parts may run concurrently)
   size_t sort_scratch_bytes;
+  ProjBwd pj;             // the projected-vector path's regions (proj_ok dims), in place of all but the grouping's
   size_t total;
 };
 
@@ -1253,9 +1301,32 @@ struct BwdWs {
 constexpr int64_t MERGE_DW_APART_ROWS = 65536;
 bool merge_dw_apart(int64_t Q) { return Q >= MERGE_DW_APART_ROWS; }
 
-BwdWs carve_bwd(void* base, const AttnShape& s, int64_t max_rows) {
+// Where the projected-vector path applies: its own regions and those of the d M' grouping.
+BwdWs carve_bwd_proj(void* base, const mtgnn_dims* d, int64_t max_q, int64_t max_rows) {
+  const ProjShape s(d, max_q);
+  BwdWs v{};
+  v.pj = carve_proj_bwd(base, s);
+  char* w = (char*)base + v.pj.total;
+  auto take = [&](size_t bytes) { char* r = w; w += a256(bytes); return r; };
+  const int64_t n_occ = s.Q + s.P, ntiles = cdiv(n_occ, SEG_TILE), mr = max_rows > 0 ? max_rows : 1;
+  v.head = (float*)take(sizeof(float) * ntiles * s.dm);
+  v.tail = (float*)take(sizeof(float) * ntiles * s.dm);
+  v.keys = (uint32_t*)take(sizeof(uint32_t) * n_occ);
+  v.vals = (uint32_t*)take(sizeof(uint32_t) * n_occ);
+  v.seg_lo = (int32_t*)take(sizeof(int32_t) * mr);
+  v.seg_hi = (int32_t*)take(sizeof(int32_t) * mr);
+  v.row_of = (int32_t*)take(sizeof(int32_t) * s.N);
+  v.sort_scratch_bytes = a256(radix_sort_ws_bytes(n_occ));
+  v.sort_scratch = take(v.sort_scratch_bytes);
+  v.total = (size_t)(w - (char*)base);
+  return v;
+}
+
+BwdWs carve_bwd(void* base, const mtgnn_dims* d, int64_t max_q, int64_t max_rows) {
+  if (proj_ok(d)) return carve_bwd_proj(base, d, max_q, max_rows);
+  const AttnShape s(d, max_q);
   char* w = (char*)base;
-  BwdWs v;
+  BwdWs v{};
   auto take = [&](size_t bytes) { char* r = w; w += a256(bytes); return r; };
   const int64_t n_occ = s.Q + s.P;
   const int64_t ntiles = cdiv(n_occ, SEG_TILE);
@@ -1364,7 +1435,10 @@ mtgnn_status segsum_rows(const uint32_t* skeys, const uint32_t* svals, int64_t n
   return MTGNN_OK;
 }
 
-size_t attn_save_bytes(const mtgnn_dims* d, int64_t max_q) { return carve_save(nullptr, AttnShape(d, max_q)).total; }
+size_t attn_save_bytes(const mtgnn_dims* d, int64_t max_q) {
+  if (proj_ok(d)) return carve_proj_save(nullptr, ProjShape(d, max_q)).total;
+  return carve_save(nullptr, AttnShape(d, max_q)).total;
+}
 
 size_t attn_fwd_ws(const mtgnn_dims*, int64_t max_q) { return scan_ws_bytes(max_q); }
 
@@ -1372,6 +1446,7 @@ mtgnn_status attn_prepare_weights_impl(const mtgnn_attn_params* p, const float* 
                                        const mtgnn_dims* d, void* save, hipStream_t s, const PadCopy* more,
                                        int n_more) {
   if (n_more < 0 || n_more > 4) return MTGNN_EINVAL;
+  if (proj_ok(d)) return proj_prepare_weights(p, tw, tb, d, save, s, more, n_more);
   const AttnShape sh(d, 0);
   const AttnSave sv = carve_save(save, sh);
   if (merge_fused_ok(d->dtype, sh.da, sh.dm)) {   // float32: one launch for every copy
@@ -1406,6 +1481,7 @@ mtgnn_status attn_prepare_weights_impl(const mtgnn_attn_params* p, const float* 
 
 mtgnn_status attn_prepare_slots_impl(const int32_t* nbr, const int32_t* n_q, int64_t max_q, const mtgnn_dims* d,
                                      void* save, void* ws, size_t ws_bytes, hipStream_t s) {
+  if (proj_ok(d)) return MTGNN_OK;   // slots stay where they were sampled: no counts or offsets
   const AttnShape sh(d, max_q);
   const AttnSave sv = carve_save(save, sh);
   k_pair_counts<<<(unsigned)cdiv(max_q, 256), 256, 0, s>>>(nbr, n_q, max_q, sh.k, sv.cnt);
@@ -1433,6 +1509,8 @@ mtgnn_status attn_fwd_prepared_impl(const int32_t* q_node, const float* q_t, con
                                     const float* edge_feat, const float* tw, const float* tb,
                                     const mtgnn_attn_params* p, const mtgnn_dims* d, float* z, void* save,
                                     hipStream_t s) {
+  if (proj_ok(d))
+    return proj_fwd(q_node, q_t, n_q, max_q, nbr, nt, neid, memory, edge_feat, tw, tb, p, d, z, save, s);
   const AttnShape sh(d, max_q);
   const AttnSave sv = carve_save(save, sh);
   const int bf = d->dtype == MTGNN_BF16 ? 1 : 0;
@@ -1496,7 +1574,7 @@ mtgnn_status attn_fwd_prepared_impl(const int32_t* q_node, const float* q_t, con
 }
 
 size_t attn_bwd_ws(const mtgnn_dims* d, int64_t max_q, int64_t max_rows) {
-  return carve_bwd(nullptr, AttnShape(d, max_q), max_rows).total;
+  return carve_bwd(nullptr, d, max_q, max_rows).total;
 }
 
 namespace {
@@ -1509,16 +1587,20 @@ namespace {
 // segment bounds.  Reads only forward outputs and the updated-row list, so it may run before
 // any gradient exists.  *skeys / *svals: the buffers holding the sorted pairs.
 mtgnn_status attn_bwd_dmem_group(const int32_t* q_node, const int32_t* n_q, int64_t max_q, const int32_t* nbr,
-                                 const AttnShape& sh, const AttnSave& sv, const BwdWs& b, const int32_t* uniq,
+                                 bool proj, const AttnShape& sh, const AttnSave& sv, const BwdWs& b, const int32_t* uniq,
                                  const int32_t* n_rows, int64_t max_rows, uint32_t** skeys, uint32_t** svals,
                                  hipStream_t s) {
   const int64_t n_occ = sh.Q + sh.P;
   const uint32_t sentinel = (uint32_t)max_rows;
   k_row_map<<<(unsigned)cdiv(max_rows, 256), 256, 0, s>>>(uniq, n_rows, max_rows, b.row_of, b.seg_lo, b.seg_hi);
   MTGNN_CHECK_LAUNCH("row_map");
-  k_occ_keys<<<(unsigned)cdiv(n_occ, 256), 256, 0, s>>>(q_node, nbr, sv.cnt, sv.pair_off, n_q, max_q, sh.k,
-                                                         sv.n_valid, sh.P, uniq, n_rows, max_rows, b.row_of, sentinel,
-                                                         b.keys, b.vals);
+  if (proj)
+    k_occ_keys_grid<<<(unsigned)(cdiv(max_q, 256) + cdiv(max_q, 256 / sh.k)), 256, 0, s>>>(
+        q_node, nbr, n_q, max_q, sh.k, cdiv(max_q, 256), uniq, n_rows, max_rows, b.row_of, sentinel, b.keys, b.vals);
+  else
+    k_occ_keys<<<(unsigned)cdiv(n_occ, 256), 256, 0, s>>>(q_node, nbr, sv.cnt, sv.pair_off, n_q, max_q, sh.k,
+                                                           sv.n_valid, sh.P, uniq, n_rows, max_rows, b.row_of,
+                                                           sentinel, b.keys, b.vals);
   MTGNN_CHECK_LAUNCH("occ_keys");
   *skeys = b.keys;
   *svals = b.vals;
@@ -1530,7 +1612,7 @@ mtgnn_status attn_bwd_dmem_group(const int32_t* q_node, const int32_t* n_q, int6
 
 // d M' grouping, second half: per-row sums of [dh_q | dK | dV] over the sorted occurrences, in a
 // fixed order, then d M' = (sum of dh_q) + (sum of dK|dV) W_kv[:, :dm].
-mtgnn_status attn_bwd_dmem_sum(int64_t max_q, const AttnShape& sh, const AttnSave& sv, const BwdWs& b,
+mtgnn_status attn_bwd_dmem_sum(int64_t max_q, bool proj, const AttnShape& sh, const AttnSave& sv, const BwdWs& b,
                                const uint32_t* skeys, const uint32_t* svals, const int32_t* n_rows, int64_t max_rows,
                                int wt, float* d_mem, hipStream_t s) {
   const int64_t Q = sh.Q, P = sh.P, ldm = sh.da + sh.dm;
@@ -1538,17 +1620,22 @@ mtgnn_status attn_bwd_dmem_sum(int64_t max_q, const AttnShape& sh, const AttnSav
   {
     const int64_t n_occ = Q + P;
     const uint32_t sentinel = (uint32_t)max_rows;
-    SegCtx c;
+    SegCtx c{};
     c.keys = (uint32_t*)skeys; c.vals = (uint32_t*)svals; c.n_occ = n_occ; c.sentinel = sentinel; c.max_q = max_q;
     c.seg_lo = b.seg_lo; c.seg_hi = b.seg_hi;
-    c.dhq = b.dm_in + da; c.ldq = ldm; c.dkv = b.dKV; c.dm = dm; c.w2 = 2 * da;
+    c.dm = dm;
+    if (proj) {
+      c.dhq = b.pj.dhq; c.ldq = dm; c.dx = b.pj.dx;
+    } else {
+      c.dhq = b.dm_in + da; c.ldq = ldm; c.dkv = b.dKV; c.w2 = 2 * da;
+    }
     c.S = b.S; c.D = d_mem; c.head = b.head; c.tail = b.tail; c.tile = SEG_TILE;
     const int64_t ntiles = cdiv(n_occ, SEG_TILE);
     const unsigned gt = (unsigned)cdiv(ntiles, 4);
-    if (dm % 4 == 0 && da % 4 == 0 && dm + 2 * da <= 512) {   // 16-byte aligned rows and groups
+    if (dm % 4 == 0 && da % 4 == 0 && dm + 2 * da <= 512 && ((uintptr_t)d_mem & 15) == 0) {   // 16-byte groups
       k_segsum_tiles_v4<<<gt, 256, 0, s>>>(c);
     } else {
-      switch (cdiv(dm + 2 * da, 64)) {   // column chunks per lane (validation keeps the width <= 512)
+      switch (cdiv(dm + c.w2, 64)) {   // column chunks per lane (validation keeps the width <= 512)
         case 1: k_segsum_tiles<1><<<gt, 256, 0, s>>>(c); break;
         case 2: k_segsum_tiles<2><<<gt, 256, 0, s>>>(c); break;
         case 3: k_segsum_tiles<3><<<gt, 256, 0, s>>>(c); break;
@@ -1562,6 +1649,7 @@ mtgnn_status attn_bwd_dmem_sum(int64_t max_q, const AttnShape& sh, const AttnSav
     MTGNN_CHECK_LAUNCH("segsum_tiles");
     launch_segsum_fixup(c, n_rows, max_rows, ntiles, s);
     MTGNN_CHECK_LAUNCH("segsum_fixup");
+    if (proj) return MTGNN_OK;
     const int W = dm + 2 * da;
     if (qproj_fused_ok(wt, da, dm, sh.dt))
       MTGNN_TRY(dmem_dx_fused(b.S, W, sv.merge_w, d_mem, n_rows, max_rows, da, dm, sh.dt, s));
@@ -1646,12 +1734,13 @@ mtgnn_status attn_bwd_group_impl(const int32_t* q_node, const int32_t* n_q, int6
                                  const void* save, const int32_t* uniq, const int32_t* n_rows, int64_t max_rows,
                                  const mtgnn_dims* d, void* ws, size_t ws_bytes, hipStream_t s) {
   const AttnShape sh(d, max_q);
-  const AttnSave sv = carve_save((void*)save, sh);
-  const BwdWs b = carve_bwd(ws, sh, max_rows);
+  const bool proj = proj_ok(d);
+  const AttnSave sv = proj ? AttnSave{} : carve_save((void*)save, sh);
+  const BwdWs b = carve_bwd(ws, d, max_q, max_rows);
   if (ws_bytes < b.total) return MTGNN_EWORKSPACE;
   if (max_rows == 0) return MTGNN_OK;
   uint32_t *skeys = nullptr, *svals = nullptr;
-  return attn_bwd_dmem_group(q_node, n_q, max_q, nbr, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s);
+  return attn_bwd_dmem_group(q_node, n_q, max_q, nbr, proj, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s);
 }
 
 mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_t* n_q, int64_t max_q,
@@ -1660,11 +1749,10 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
                            const mtgnn_attn_params* p, const mtgnn_dims* d, mtgnn_attn_grads* g, float* d_mem,
                            float* d_time_w, float* d_time_b, void* ws, size_t ws_bytes, hipStream_t s,
                            hipStream_t s_dmem, hipEvent_t fork, hipEvent_t join, bool grouped) {
-  (void)q_t;
-  (void)nt;
   const AttnShape sh(d, max_q);
-  const AttnSave sv = carve_save((void*)save, sh);
-  const BwdWs b = carve_bwd(ws, sh, max_rows);
+  const bool proj = proj_ok(d);
+  const AttnSave sv = proj ? AttnSave{} : carve_save((void*)save, sh);
+  const BwdWs b = carve_bwd(ws, d, max_q, max_rows);
   if (ws_bytes < b.total) return MTGNN_EWORKSPACE;
   const int wt = d->dtype;
   const int64_t Q = sh.Q, ldm = sh.da + sh.dm;
@@ -1687,7 +1775,7 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
       return MTGNN_EHIP;
     }
     const mtgnn_status st0 =
-        attn_bwd_dmem_group(q_node, n_q, max_q, nbr, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s_dmem);
+        attn_bwd_dmem_group(q_node, n_q, max_q, nbr, proj, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s_dmem);
     if (st0 != MTGNN_OK) {   // leave `stream` ordered after the second stream
       if (hipEventRecord(join, s_dmem) == hipSuccess) (void)hipStreamWaitEvent(s, join, 0);
       return st0;
@@ -1695,6 +1783,7 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
   }
   // data gradients down to dK|dV and dh_q, on `stream`
   auto chain = [&]() -> mtgnn_status {
+    if (proj) return proj_bwd(q_t, n_q, max_q, nbr, nt, dz, tw, tb, d, save, b.pj, s);
     // merge MLP: z = W_2 a1 + b_2, a1 = relu(m1), m1 = W_1 m_in + b_1
     // (their weight gradients run as one batch after the score backward)
     // output projection: o = W_o attn + b_o   (do = dm_in[:, :da])
@@ -1751,15 +1840,19 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
       MTGNN_TRY(linear_dx(b.dqv, da, p->W_q, wt, sh.Dq, b.dm_in + da, ldm, Q, n_q, da, dm, true, s));
     return MTGNN_OK;
   };
+  auto params = [&]() -> mtgnn_status {
+    if (proj) return proj_params(n_q, max_q, dz, tw, tb, p, d, save, b.pj, g, d_time_w, d_time_b, s);
+    return attn_bwd_params(n_q, sh, sv, b, dz, tw, tb, p, wt, g, d_time_w, d_time_b, s);
+  };
   if (const mtgnn_status st1 = chain(); st1 != MTGNN_OK) {
     if (overlap && join && hipEventRecord(join, s_dmem) == hipSuccess) (void)hipStreamWaitEvent(s, join, 0);
     return st1;
   }
   if (!overlap) {
-    MTGNN_TRY(attn_bwd_params(n_q, sh, sv, b, dz, tw, tb, p, wt, g, d_time_w, d_time_b, s));
+    MTGNN_TRY(params());
     if (max_rows > 0) {
-      MTGNN_TRY(attn_bwd_dmem_group(q_node, n_q, max_q, nbr, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s));
-      MTGNN_TRY(attn_bwd_dmem_sum(max_q, sh, sv, b, skeys, svals, n_rows, max_rows, wt, d_mem, s));
+      MTGNN_TRY(attn_bwd_dmem_group(q_node, n_q, max_q, nbr, proj, sh, sv, b, uniq, n_rows, max_rows, &skeys, &svals, s));
+      MTGNN_TRY(attn_bwd_dmem_sum(max_q, proj, sh, sv, b, skeys, svals, n_rows, max_rows, wt, d_mem, s));
     }
     return MTGNN_OK;
   }
@@ -1771,14 +1864,14 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
     set_hip_error(e, "attn_bwd fork");
     return MTGNN_EHIP;
   }
-  MTGNN_TRY(attn_bwd_dmem_sum(max_q, sh, sv, b, skeys, svals, n_rows, max_rows, wt, d_mem, s_dmem));
-  if (!join) return attn_bwd_params(n_q, sh, sv, b, dz, tw, tb, p, wt, g, d_time_w, d_time_b, s);
+  MTGNN_TRY(attn_bwd_dmem_sum(max_q, proj, sh, sv, b, skeys, svals, n_rows, max_rows, wt, d_mem, s_dmem));
+  if (!join) return params();
   e = hipEventRecord(join, s_dmem);
   if (e != hipSuccess) {
     set_hip_error(e, "attn_bwd join");
     return MTGNN_EHIP;
   }
-  const mtgnn_status st = attn_bwd_params(n_q, sh, sv, b, dz, tw, tb, p, wt, g, d_time_w, d_time_b, s);
+  const mtgnn_status st = params();
   e = hipStreamWaitEvent(s, join, 0);   // even after a failure, leave `stream` ordered after the second stream
   if (e != hipSuccess) {
     set_hip_error(e, "attn_bwd join wait");

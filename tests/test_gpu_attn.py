@@ -1,0 +1,150 @@
+"""The temporal attention, both directions, against a float64 evaluation at the edges of its kernels' sizes.
+
+Widths that are one and several column groups, padded heads (head width not a multiple of 4), padded and
+odd edge features, one and many slots (more than a half-wave's 32, a full wave's 64), 16- and 32-row blocks with
+ragged ends, queries without slots and with a gap in their slots, rows at unaligned addresses, time
+arguments past the fast range of the encoding, and dims that only the general path takes.
+Gate: 1e-4 of each tensor's largest value in float32 (sums of at most a few hundred products: about
+1e-6), 2e-2 in bfloat16 (a stored value that rounds the other way moves by 2^-8).
+"""
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_16305_amd import mtgnn as M
+from tests._gpu import log, needs_gpu, rel_err
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+NAMES = ("W_q", "W_k", "W_v", "W_o", "W_1", "W_2", "b_q", "b_k", "b_v", "b_o", "b_1", "b_2")
+
+
+def _rnd(x, bf16):
+    return x + (x.detach().float().bfloat16().double() - x.detach()) if bf16 else x
+
+
+def _reference(p, mem, x, q_node, q_t, nbr, nt, neid, tw, tb, dz, H, bf16, uniq):
+    """float64 on the CPU: z, the gradients and d_mem."""
+    q64 = {n: v.double().requires_grad_() for n, v in p.items()}
+    on = np.cumprod(nbr.numpy() >= 0, axis=1).astype(bool)
+    on = torch.from_numpy(on)
+    k, da = nbr.shape[1], p["W_q"].shape[0]
+    m64 = mem.double().requires_grad_()
+    w64, b64 = tw.double().requires_grad_(), tb.double().requires_grad_()
+
+    def phi(dt):
+        arg32 = tw * dt[..., None]
+        arg32 = arg32 + tb
+        arg = w64 * dt[..., None].double() + b64
+        return _rnd(torch.cos(arg + (arg32.double() - arg).detach()), bf16)
+
+    lin = lambda v, n: v @ q64["W_" + n].T + q64["b_" + n]   # noqa: E731
+    Q = q_node.numel()
+    hq = m64[q_node.long()]
+    q = lin(torch.cat([hq, phi(torch.zeros(Q))], 1), "q").view(Q, 1, H, da // H)
+    kv = [m64[nbr.clamp(min=0).long()]]
+    if x is not None:
+        kv.append(_rnd(x[neid.clamp(min=0).long()].double(), bf16))
+    kv = torch.cat(kv + [phi(torch.where(on, q_t[:, None] - nt, torch.zeros(())))], 2)
+    K, V = lin(kv, "k").view(Q, k, H, -1), lin(kv, "v").view(Q, k, H, -1)
+    s = ((q * K).sum(3) / math.sqrt(da // H)).masked_fill(~on[..., None], -1e300)
+    e = torch.exp(s - s.detach().amax(1, keepdim=True)) * on[..., None]
+    a = ((e / e.sum(1, keepdim=True).clamp(min=1e-300))[..., None] * V).sum(1).reshape(Q, da)
+    o = _rnd(lin(_rnd(a, bf16), "o"), bf16)
+    z = lin(_rnd(torch.relu(lin(torch.cat([o, hq], 1), "1")), bf16), "2")
+    z.backward(dz.double())
+    g = {n: q64[n].grad.numpy() for n in NAMES}
+    g.update(time_w=w64.grad.numpy(), time_b=b64.grad.numpy(), d_mem=m64.grad[uniq.long()].numpy())
+    return z.detach().numpy(), g
+
+
+#        H   dm   dt   de   da   k  max_q  n_q  dtype unaligned span
+CASES = [(1, 4, 4, 0, 4, 1, 5, 5, "f32", False, 10.0),
+         (2, 12, 8, 1, 12, 3, 33, 31, "f32", True, 1e5),
+         (2, 100, 100, 3, 100, 20, 70, 66, "f32", False, 1e5),
+         (1, 128, 128, 190, 128, 7, 40, 40, "f32", True, 1e3),
+         (2, 128, 64, 256, 128, 64, 17, 17, "f32", False, 5e7),
+         (2, 36, 100, 16, 20, 33, 48, 47, "f32", False, 1e4),
+         (1, 32, 32, 2, 32, 5, 16_500, 16_400, "f32", True, 1e5),
+         (2, 100, 100, 4, 100, 10, 16_400, 16_390, "f32", False, 1e5),
+         (2, 100, 100, 0, 100, 20, 50, 50, "bf16", False, 1e5),
+         (1, 32, 32, 5, 32, 4, 35, 33, "bf16", True, 1e6),
+         (4, 100, 100, 6, 100, 9, 45, 44, "f32", False, 1e4),      # general path: four heads
+         (2, 30, 14, 3, 22, 6, 40, 39, "f32", False, 1e3)]         # general path: odd widths
+
+
+@pytest.mark.parametrize("H,dm,dt,de,da,k,max_q,n_q,dtype,unaligned,span", CASES)
+def test_attention_sizes(H, dm, dt, de, da, k, max_q, n_q, dtype, unaligned, span):
+    bf16 = dtype == "bf16"
+    rng = np.random.default_rng(H * 1000 + dm * 7 + de * 3 + k)
+    N, E = 97, 211
+    store = torch.bfloat16 if bf16 else torch.float32
+    log(f"[attn] H {H} dm {dm} dt {dt} de {de} da {da} k {k} queries {n_q}/{max_q} {dtype}")
+    u = lambda *s: torch.from_numpy(rng.uniform(-1, 1, s).astype(np.float32))   # noqa: E731
+    kv = dm + de + dt
+    shapes = dict(W_q=(da, dm + dt), W_k=(da, kv), W_v=(da, kv), W_o=(da, da), W_1=(da, da + dm), W_2=(da, da))
+    p = {}
+    for n, (o, i) in shapes.items():
+        p[n] = (u(o, i) * math.sqrt(6.0 / (o + i))).to(store)
+        p["b" + n[1:]] = u(o) * 0.1
+    tw = torch.from_numpy((10.0 ** (-6.0 * np.arange(dt) / max(dt - 1, 1))).astype(np.float32))
+    tb = u(dt)
+    mem, x = u(N, dm).to(store), (u(E, de) if de else None)
+    q_node = torch.from_numpy(rng.integers(0, N, max_q).astype(np.int32))
+    cnt = rng.integers(0, k + 1, max_q)
+    nbr = rng.integers(0, N, (max_q, k)).astype(np.int32)
+    nbr[np.arange(k)[None] >= cnt[:, None]] = -1
+    gap = rng.random(max_q) < 0.1
+    nbr[gap, k // 2] = -1   # slots behind a gap do not count
+    nbr = torch.from_numpy(nbr)
+    neid = torch.from_numpy(rng.integers(0, E, (max_q, k)).astype(np.int32))
+    q_t = torch.from_numpy((span * (1 + rng.random(max_q))).astype(np.float32))
+    nt = torch.from_numpy((span * rng.random((max_q, k))).astype(np.float32))
+    dz = u(max_q, da) / max_q
+    uniq = torch.from_numpy(rng.permutation(N)[:60].astype(np.int32))
+    n_rows = 57
+    z_ref, g_ref = _reference(p, mem, x, q_node[:n_q], q_t[:n_q], nbr[:n_q], nt[:n_q], neid[:n_q], tw, tb, dz[:n_q], H,
+                              bf16, uniq[:n_rows])
+
+    def dev(t, shift=False):
+        if t is None:
+            return None
+        if not shift:
+            return t.cuda()
+        flat = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        flat[1:] = t.reshape(-1)
+        return flat[1:].view(t.shape)
+
+    pd = {n: dev(v) for n, v in p.items()}
+    d = M.dims(N, dm, dt, de, da, H, k, M.BF16 if bf16 else M.F32)
+    c_q, c_r = (torch.tensor([n], dtype=torch.int32, device="cuda") for n in (n_q, n_rows))
+    nan = lambda *s: torch.full(s, math.nan, device="cuda")   # noqa: E731
+    z, d_mem = nan(max_q, da), nan(60, dm)
+    g = {n: nan(*p[n].shape) for n in NAMES}
+    g.update(time_w=nan(dt), time_b=nan(dt))
+    save = M.alloc_bytes(M.save_bytes(M.OP_TEMPORAL_ATTN, d, 0, max_q)).fill_(255)
+    ws = M.alloc_bytes(max(M.workspace_bytes(M.OP_TEMPORAL_ATTN, d, 0, max_q),
+                           M.workspace_bytes(M.OP_TEMPORAL_ATTN_BWD, d, 60, max_q))).fill_(255)
+    args = [dev(t) for t in (q_node, q_t)] + [c_q, max_q] + [dev(t) for t in (nbr, nt)]
+    td = dev(tw), dev(tb)
+    M.mtgnn_temporal_attn(*args, dev(neid), dev(mem, unaligned), dev(x, unaligned), *td, M.attn_params(pd, d), d, z, save, ws)
+    M.mtgnn_temporal_attn_bwd(*args, dev(dz, unaligned), save, dev(uniq), c_r, 60, *td, M.attn_params(pd, d), d,
+                              M.attn_grads(g), d_mem, g["time_w"], g["time_b"], ws)
+    torch.cuda.synchronize()
+    errs = {"z": rel_err(z[:n_q].cpu().numpy(), z_ref)}
+    g["d_mem"] = d_mem[:n_rows]
+    for n, r in g_ref.items():
+        got = g[n].cpu().numpy()
+        if n == "b_k" or (n == "W_k" and k == 1):   # one slot: no score gradient but rounding
+            errs[n] = float(np.abs(got).max() / np.abs(g_ref["W_v"]).max())
+        elif n in ("W_q", "b_q") and k == 1:
+            errs[n] = float(np.abs(got).max() / np.abs(g_ref["W_v"]).max())
+        else:
+            errs[n] = rel_err(got, r)
+    log("  errors: " + ", ".join(f"{n}={v:.1e}" for n, v in errs.items()))
+    assert all(math.isfinite(v) for v in errs.values()), errs
+    assert max(errs.values()) <= (2e-2 if bf16 else 1e-4), errs
+    assert torch.isnan(z[n_q:]).all()   # rows beyond the device count are left alone
