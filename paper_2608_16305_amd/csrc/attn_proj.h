@@ -24,7 +24,7 @@ struct ProjShape {
 // Whether these dims take this path (the general path of attention.hip covers the rest).
 bool proj_ok(const mtgnn_dims* d);
 
-// Packed weights (float32, MFMA fragment order), then the arrays the backward reads.
+// Packed weights (MFMA fragment order), then the arrays the backward reads.
 struct ProjSave {
   float *w[13];   // see ProjPack
   float* qc;      // [dap] the query projection's constant b_q + W_q[:, dm:] phi(0)
