@@ -304,7 +304,8 @@ def valid_slots(runner, s, w, b):
 CSRC = os.path.join(ROOT, "paper_2608_16305_amd", "csrc")
 # sources that define the hot-site kernels and their launches
 TRAFFIC_SOURCES = ("common.h", "gemm.h", "gemm.hip", "gemm_nt.hip", "gemm_nn.hip", "gemm_tn.hip", "gemm_rs.h",
-                   "gemm_rs.hip", "lds_dma.h", "attention.hip", "attn_proj.h", "attn_proj.hip")
+                   "gemm_rs.hip", "lds_dma.h", "attention.hip", "attn_proj.h", "attn_proj.hip", "bf16_split.h",
+                   "dw_split.h")
 
 
 def kernel_fingerprint():

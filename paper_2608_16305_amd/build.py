@@ -29,7 +29,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 # assembly must not spill vector registers: a spill could copy a register before
 # its LDS data has arrived.  The build fails if one of them does.  (Scalar
 # registers spilled into vector-register lanes hold no LDS data.)
-NO_SPILL = ("k_gemm_rs", "k_dw_rs", "k_dw_os")
+NO_SPILL = ("k_gemm_rs", "k_dw_rs")
 
 
 def _spilling_kernels(remarks: str) -> list:

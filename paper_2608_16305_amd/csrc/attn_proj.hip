@@ -17,6 +17,7 @@
 #include "gemm.h"
 #include "attn_proj.h"
 #include "bf16_split.h"
+#include "dw_split.h"
 
 namespace mtgnn {
 
@@ -897,147 +898,21 @@ struct DwArgs {
   const int32_t* R_dev;
 };
 
-// A row's columns as NT MFMA operands: with NT >= 4 the first four are the lane's 16-byte group (tile t
-// holds the columns 4 fr + t), the others one column each (16 t + fr); NT = 2: the 8-byte group 2 fr.
-template <int NT>
-__device__ __forceinline__ int dw_col(int t, int i) {
-  if (NT == 2) return 2 * i + t;
-  return t < 4 ? 4 * i + t : 16 * t + i;
-}
-template <int NT>
-__device__ __forceinline__ void dw_load(const float* row, int fr, int lim, float (&v)[NT]) {
-  if constexpr (NT == 2) {
-    const float2 x = *(const float2*)(row + min(2 * fr, lim - 2));
-    v[0] = x.x;
-    v[1] = x.y;
-  } else {
-    const float4 x = *(const float4*)(row + min(4 * fr, lim - 4));
-    v[0] = x.x;
-    v[1] = x.y;
-    v[2] = x.z;
-    v[3] = x.w;
-#pragma unroll
-    for (int t = 4; t < NT; ++t) v[t] = row[min(16 * t + fr, lim - 1)];
-  }
-}
-
-// The block's waves take its rows four at a time in turn, operands straight from memory (a 4-row step of
-// two 16-byte groups per lane feeds up to 16 MFMAs), S steps in flight; their sums are added in wave order.
-template <int NI, int NJ>
-__device__ __forceinline__ void dw_body(const DwUnit q, int64_t R, float* lds) {
-  constexpr int S = NI * NJ > 30 ? 2 : 4;
-  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int fr = lane & 15, fg = lane >> 4;
-  const int64_t bi = (int)blockIdx.x - q.b_begin;
-  const int64_t steps = (R + 3) / 4;
-  const int64_t s0 = steps * bi / q.nblk, s1 = steps * (bi + 1) / q.nblk;
-  f32x4 acc[NI][NJ];
-  float cs[NI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    cs[i] = 0.f;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  float ya[S][NI], xa[S][NJ], yb[S][NI], xb[S][NJ];
-  auto load = [&](int64_t s, float (&y)[S][NI], float (&x)[S][NJ]) {
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-      const int64_t r = min(4 * (s + 4 * i) + fg, R - 1);   // 4 waves: every fourth step
-      dw_load<NI>(q.Y + r * q.ldy, fr, q.ylim, y[i]);
-      dw_load<NJ>(q.X + r * q.ldx, fr, q.xlim, x[i]);
-    }
-  };
-  auto mma = [&](int64_t s, float (&y)[S][NI], float (&x)[S][NJ]) {
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-      const int64_t st = s + 4 * i;
-      const bool on = st < s1 && 4 * st + fg < R;   // a step past the range adds zeros
-#pragma unroll
-      for (int t = 0; t < NI; ++t) {
-        y[i][t] = on ? y[i][t] : 0.f;
-        cs[t] += y[i][t];
-      }
-#pragma unroll
-      for (int t = 0; t < NJ; ++t) x[i][t] = on ? x[i][t] : 0.f;
-#pragma unroll
-      for (int a = 0; a < NI; ++a)
-#pragma unroll
-        for (int b = 0; b < NJ; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[i][a], x[i][b], acc[a][b], 0, 0, 0);
-    }
-  };
-  if (s0 + wid < s1) {
-    load(s0 + wid, ya, xa);
-    for (int64_t s = s0 + wid; s < s1; s += 8 * S) {
-      if (s + 4 * S < s1) load(s + 4 * S, yb, xb);
-      mma(s, ya, xa);
-      if (s + 4 * S < s1) {
-        if (s + 8 * S < s1) load(s + 8 * S, ya, xa);
-        mma(s + 4 * S, yb, xb);
-      }
-    }
-  }
-  // waves 1..3 hand their sums to wave 0 in turn
-  float* lsum = lds + NI * NJ * 256;
-  for (int w = 1; w < 4; ++w) {
-    __syncthreads();
-    if (wid == w) {
-#pragma unroll
-      for (int a = 0; a < NI; ++a) {
-#pragma unroll
-        for (int b = 0; b < NJ; ++b) *(f32x4*)(lds + ((a * NJ + b) * 64 + lane) * 4) = acc[a][b];
-        lsum[a * 64 + lane] = cs[a];
-      }
-    }
-    __syncthreads();
-    if (wid == 0) {
-#pragma unroll
-      for (int a = 0; a < NI; ++a) {
-#pragma unroll
-        for (int b = 0; b < NJ; ++b) acc[a][b] += *(const f32x4*)(lds + ((a * NJ + b) * 64 + lane) * 4);
-        cs[a] += lsum[a * 64 + lane];
-      }
-    }
-  }
-  if (wid != 0) return;
-  const int64_t per = (int64_t)q.n * q.m + (q.db ? q.n : 0);
-  float* out = q.part + bi * per;
-#pragma unroll
-  for (int a = 0; a < NI; ++a) {
-#pragma unroll
-    for (int b = 0; b < NJ; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = dw_col<NI>(a, 4 * fg + r), j = dw_col<NJ>(b, fr);
-        if (i < q.n && j < q.m) out[(int64_t)i * q.m + j] = acc[a][b][r];
-      }
-    float v = cs[a];
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    const int i = dw_col<NI>(a, fr);
-    if (q.db && fg == 0 && i < q.n) out[(int64_t)q.n * q.m + i] = v;
-  }
-}
-
-constexpr int DW_LDS = 7 * 7 * 256 + 7 * 64;
-
 __global__ __launch_bounds__(256, 1) void k_proj_dw(DwArgs a) {
   __shared__ __attribute__((aligned(16))) float lds[DW_LDS];
   int u = 0;
   while (u + 1 < a.n && (int)blockIdx.x >= a.u[u + 1].b_begin) ++u;
   const DwUnit q = a.u[u];
-  const int64_t R = eff_count(a.R, a.R_dev);
-  if (q.n <= 32) {
-    if (q.m <= 64) dw_body<2, 4>(q, R, lds);
-    else dw_body<2, 7>(q, R, lds);
-  } else if (q.n <= 64) {
-    if (q.m <= 64) dw_body<4, 4>(q, R, lds);
-    else dw_body<4, 7>(q, R, lds);
-  } else {
-    if (q.m <= 64) dw_body<7, 4>(q, R, lds);
-    else dw_body<7, 7>(q, R, lds);
-  }
+  const int64_t R = eff_count(a.R, a.R_dev), steps = (R + 31) / 32, bi = (int)blockIdx.x - q.b_begin;
+  float* part = q.part + bi * ((int64_t)q.n * q.m + (q.db ? q.n : 0));
+  dw_split_any<1>(
+      q.n, q.m, q.Y, q.ldy, q.ylim, q.X, q.ldx, q.xlim, R, steps * bi / q.nblk, steps * (bi + 1) / q.nblk, lds,
+      [&](int i, int j, float v) {
+        if (i < q.n && j < q.m) part[(int64_t)i * q.m + j] = v;
+      },
+      [&](int i, float v) {
+        if (q.db && i < q.n) part[(int64_t)q.n * q.m + i] = v;
+      });
 }
 
 // Where a unit's sums go: row i to the weight's row (i0 + i) with the padding of the heads taken out

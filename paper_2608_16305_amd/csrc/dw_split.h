@@ -1,0 +1,188 @@
+// Weight gradients (sums over rows of products of two rows' columns) on the bfloat16 matrix instructions, float32
+// operands split into three parts each (bf16_split.h).
+#pragma once
+
+#include "bf16_split.h"
+#include "gemm.h"
+
+namespace mtgnn {
+
+// A row's columns as NT column tiles of 16: the lane's 16-byte group 4 fr + t for the first four, 64 + 3 fr + t - 4
+// for the other three; NT = 2: the 8-byte group 2 fr + t.  One load a row and group.
+template <int NT>
+__device__ __forceinline__ int dw_col(int t, int i) {
+  if (NT == 2) return 2 * i + t;
+  return t < 4 ? 4 * i + t : 64 + 3 * i + t - 4;
+}
+// Groups 0 (tiles 0..3, or both of NT = 2) and 1 (tiles 4..6) of rows r .. r + 7 (those < R; zero past them), the
+// columns clamped to the first lim (what lies past a unit's columns is never stored).
+template <int NT, int G>
+__device__ __forceinline__ void dw_load(const float* p, int64_t ld, int64_t r, int64_t R, int fr, int lim,
+                                        float (&v)[NT][8]) {
+  constexpr int T0 = G ? 4 : 0, T1 = G ? 7 : NT < 4 ? NT : 4;
+  if constexpr (T0 < NT) {
+    const int c = G ? min(64 + 3 * fr, lim - 3) : min(T1 * fr, lim - T1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float* row = p + min(r + e, R - 1) * ld + c;
+#pragma unroll
+      for (int t = T0; t < T1; ++t) v[t][e] = row[t - T0];
+    }
+  }
+}
+template <int NT, int G>
+__device__ __forceinline__ void dw_zero(int64_t r, int64_t R, float (&v)[NT][8]) {   // rows past R, as loaded
+  constexpr int T0 = G ? 4 : 0, T1 = G ? 7 : NT < 4 ? NT : 4;
+  if constexpr (T0 < NT) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int t = T0; t < T1; ++t) v[t][e] = r + e < R ? v[t][e] : 0.f;
+  }
+}
+
+// The lane whose group 1 straddles the last column has loaded the columns that end there: its values move to their
+// places.  dw_ragged: whether there is such a lane.
+template <int NT>
+__device__ __forceinline__ bool dw_ragged(int lim) { return NT > 4 && lim > 64 && (lim - 64) % 3 != 0; }
+template <int NT>
+__device__ __forceinline__ void dw_shift(int fr, int lim, float (&v)[NT][8]) {
+  if constexpr (NT > 4) {
+    const int sh = 64 + 3 * fr + 3 - lim;   // 1 or 2 where it matters
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float a = v[4][e], b = v[5][e], c = v[6][e];
+      v[4][e] = sh == 1 ? b : sh == 2 ? c : a;
+      v[5][e] = sh == 1 ? c : b;
+    }
+  }
+}
+
+// The block's waves take its rows 32 at a time in turn, operands straight from memory: lane (fr, fg) holds rows
+// 8 fg .. 8 fg + 7 of a step, each column of Y and X split into three bfloat16 parts, and a pair of tiles takes
+// six 16x16x32 products (bf16_split.h) where float32 instructions take eight of twice the time.  A group's
+// next rows are requested as soon as its parts are made.  G = 2: waves w, w + 2 take the column group w (the
+// caller passes each wave its own X), G = 1: all four share one.  A group's sums are added in wave order.
+// Matrix time and the operands' reads bound it about equally.  Against 16x16x4 float32 instructions: the
+// attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us, of 12,000 rows 46 -> 34 us.
+template <int NI, int NJ, int G, class Out, class Bias>
+__device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, const float* X, int64_t ldx, int xlim,
+                                         int64_t R, int64_t s0, int64_t s1, float* lds, Out out, Bias bias) {
+  constexpr int NW = 4 / G;   // waves of a group
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wid % G, mine = wid / G;
+  const int fr = lane & 15, fg = lane >> 4;
+  f32x4 acc[NI][NJ];
+  float cs[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    cs[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  float y[NI][8], x[NJ][8];
+  if (s0 + mine < s1) {
+    const int64_t r = 32 * (s0 + mine) + 8 * fg;
+    dw_load<NJ, 0>(X, ldx, r, R, fr, xlim, x);
+    dw_load<NJ, 1>(X, ldx, r, R, fr, xlim, x);
+    dw_load<NI, 0>(Y, ldy, r, R, fr, ylim, y);
+    dw_load<NI, 1>(Y, ldy, r, R, fr, ylim, y);
+  }
+  for (int64_t s = s0 + mine; s < s1; s += NW) {
+    const int64_t r = 32 * s + 8 * fg, rn = min(32 * (s + NW), R - 1) + 8 * fg;   // the next step's (in range) rows
+    if (32 * s + 32 > R) {   // the last, ragged step
+      dw_zero<NJ, 0>(r, R, x);
+      dw_zero<NJ, 1>(r, R, x);
+      dw_zero<NI, 0>(r, R, y);
+      dw_zero<NI, 1>(r, R, y);
+    }
+    if (dw_ragged<NJ>(xlim)) dw_shift<NJ>(fr, xlim, x);
+    if (dw_ragged<NI>(ylim)) dw_shift<NI>(fr, ylim, y);
+    Bf16Parts xp[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) xp[j] = split_bf16(x[j]);
+    dw_load<NJ, 0>(X, ldx, rn, R, fr, xlim, x);
+    dw_load<NJ, 1>(X, ldx, rn, R, fr, xlim, x);
+    auto tile = [&](int i) {
+      const Bf16Parts yp = split_bf16(y[i]);
+      float c = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c += y[i][e];
+      cs[i] += c;
+      // the small products first; a term of all tiles before the next term of one (the chains don't wait)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.lo, xp[j].hi, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].lo, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mid, xp[j].mid, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mid, xp[j].hi, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].mid, acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].hi, acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < (NI < 4 ? NI : 4); ++i) tile(i);
+    dw_load<NI, 0>(Y, ldy, rn, R, fr, ylim, y);
+    if constexpr (NI > 4) {
+#pragma unroll
+      for (int i = 4; i < NI; ++i) tile(i);
+      dw_load<NI, 1>(Y, ldy, rn, R, fr, ylim, y);
+    }
+  }
+  // the waves' sums meet in LDS a tile row at a time (two buffers, so that one barrier a row is enough), and a
+  // group's waves add and store its tiles in turn
+  float* lsum = lds + 2 * 4 * 7 * 256;
+#pragma unroll
+  for (int a = 0; a < NI; ++a) {
+    float* buf = lds + (a & 1) * 4 * 7 * 256;
+#pragma unroll
+    for (int b = 0; b < NJ; ++b) *(f32x4*)(buf + ((wid * NJ + b) * 64 + lane) * 4) = acc[a][b];
+    lsum[(a * 4 + wid) * 64 + lane] = cs[a];
+    __syncthreads();
+    for (int b = mine; b < NJ; b += NW) {
+      f32x4 v = *(const f32x4*)(buf + ((grp * NJ + b) * 64 + lane) * 4);
+#pragma unroll
+      for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + lane) * 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
+    }
+    if (wid == 3) {   // the last wave: it has the fewest tiles; group 0's sums
+      float v = lsum[a * 4 * 64 + lane];
+#pragma unroll
+      for (int l = 1; l < NW; ++l) v += lsum[(a * 4 + G * l) * 64 + lane];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (fg == 0) bias(dw_col<NI>(a, fr), v);
+    }
+  }
+}
+
+constexpr int DW_LDS = 2 * 4 * 7 * 256 + 7 * 4 * 64;   // floats
+
+// The body for the tiles that n by m outputs take (n, m at most 112).
+template <int G, class Out, class Bias>
+__device__ __forceinline__ void dw_split_any(int n, int m, const float* Y, int64_t ldy, int ylim, const float* X,
+                                             int64_t ldx, int xlim, int64_t R, int64_t s0, int64_t s1, float* lds,
+                                             Out out, Bias bias) {
+  auto run = [&](auto ni, auto nj) {
+    dw_split<decltype(ni)::value, decltype(nj)::value, G>(Y, ldy, ylim, X, ldx, xlim, R, s0, s1, lds, out, bias);
+  };
+  auto cols = [&](auto ni) {
+    if (m <= 64) run(ni, std::integral_constant<int, 4>{});
+    else run(ni, std::integral_constant<int, 7>{});
+  };
+  if (n <= 32) cols(std::integral_constant<int, 2>{});
+  else if (n <= 64) cols(std::integral_constant<int, 4>{});
+  else cols(std::integral_constant<int, 7>{});
+}
+
+}  // namespace mtgnn

@@ -70,6 +70,20 @@ def test_link_loss_ragged_width():
     assert max(errs.values()) <= 1e-4, errs
 
 
+@pytest.mark.parametrize("da", [20, 32, 36, 64, 68, 72, 76, 100, 104, 108, 112])
+@pytest.mark.parametrize("n_tar", [1, 31, 33, 257])
+def test_link_loss_tile_edges(da, n_tar):
+    """Widths at the edges of the weight gradient's column tiles (one to seven, the last columns whole and cut)
+    and target counts around its steps of 32 rows."""
+    from dataclasses import replace
+    w = replace(workload(1), d_attn=da, n_heads=2)
+    ref, loss, scores, dz, g = _run(w, 300, n_tar, seed=da + n_tar)
+    errs = {"loss": abs(loss - ref.loss) / abs(ref.loss), "dz": rel_err(dz[:3 * n_tar], ref.dz)}
+    errs.update({k: rel_err(g[k], ref.grads[k]) for k in ref.grads})
+    log(f"[link] d_attn {da}, {n_tar} targets: " + ", ".join(f"{k}={v:.1e}" for k, v in sorted(errs.items())))
+    assert max(errs.values()) <= 1e-4, errs
+
+
 @pytest.mark.parametrize("cid,max_tar,n_tar", [(3, 4_000, 3_517), (1, 200, 137)])
 def test_link_loss_overlap_bitwise(cid, max_tar, n_tar):
     """mtgnn_link_loss_overlap (W_d1's gradient on a second stream after a fork) against mtgnn_link_loss:
