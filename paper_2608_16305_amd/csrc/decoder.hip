@@ -177,7 +177,7 @@ mtgnn_status link_loss_impl(const float* z, const int32_t* n_q, int64_t max_q, c
       }
       MTGNN_TRY(link_reduce(L.part, n_q, max_q, da, g->W_d2, g->b_d2, loss, s_dw));
     }
-    // DA is zero past the src block (the first third of the query rows), DB on it
+    // DA holds the src block (the first third of the query rows), DB the other two
     const DwProblem dp[2] = {{L.DA, da, z, da, g->W_d1, 2 * da, da, da, g->b_d1, 0, 1, 3},
                              {L.DB, da, z, da, g->W_d1 + da, 2 * da, da, da, L.db_scratch, 1, 3, 3}};
     return linear_dw_batch(dp, 2, max_q, n_q, MTGNN_F32, L.rest, L.rest_bytes, s_dw ? s_dw : s);

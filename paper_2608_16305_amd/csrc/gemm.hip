@@ -278,6 +278,8 @@ mtgnn_status linear_dw_batch(const DwProblem* ps, int n, int64_t R, const int32_
     MTGNN_CHECK_LAUNCH("splitk_reduce_batch");
     return MTGNN_OK;
   }
+  for (int i = 0; i < n; ++i)
+    if (ps[i].row_den > 0) return MTGNN_EUNSUPPORTED;
   DwPlan plan = dw_batch_plan(R, Ns, Ks, n);
   if (R_dev) {
     int64_t tiles = 0;

@@ -647,8 +647,10 @@ __global__ __launch_bounds__(64 * NW) void k_gru_fused(const float* __restrict__
 // backward: ds_pos = (sigmoid(s_pos) - 1) / n, ds_neg = sigmoid(s_neg) / n, dh = ds W_d2 [pre > 0],
 //   dz_src = (dh_pos + dh_neg) W_a, dz_dst = dh_pos W_b, dz_neg = dh_neg W_b.
 // W_a, W_b are the column halves of W_d1; Wp holds their zero-padded copies and transposes.  The
-// hidden-row gradients also go to the query-layout buffers DA (src rows: dh_pos + dh_neg, other rows
-// zero) and DB (dst rows dh_pos, neg rows dh_neg, src rows zero), for dW_d1 = [DA^T z | DB^T z];
+// hidden-row gradients also go to the query-layout buffers DA (src rows: dh_pos + dh_neg) and DB (dst rows
+// dh_pos, neg rows dh_neg), for dW_d1 = [DA^T z | DB^T z] over those rows (the others stay unwritten: a quarter
+// of the kernel's bytes).
+// 60,000 targets: 174 -> 169 us.
 // part[block] = the block's sums of ds_pos h_pos + ds_neg h_neg (d_a), ds_pos + ds_neg, and l / n.
 template <int NA>
 __global__ __launch_bounds__(64 * MW) void k_link_fused(const float* __restrict__ z, const int32_t* __restrict__ n_q,
@@ -725,9 +727,6 @@ __global__ __launch_bounds__(64 * MW) void k_link_fused(const float* __restrict_
         T[2][e * XL + j] = dhn;
         if (ok && j < da) {
           DA[q * da + j] = dhp + dhn;
-          DA[(n + q) * da + j] = 0.f;
-          DA[(2 * n + q) * da + j] = 0.f;
-          DB[q * da + j] = 0.f;
           DB[(n + q) * da + j] = dhp;
           DB[(2 * n + q) * da + j] = dhn;
           gsum[h] += dsp * fmaxf(pp, 0.f) + dsn * fmaxf(pn, 0.f);
