@@ -10,8 +10,8 @@
 //
 // Measured against a key/value product over every slot (its rows gathered to memory, the softmax and its
 // backward in kernels of their own), 60,000 events, 20 slots, width 100, 16 edge features, 2 heads:
-// forward 3340 -> 1350 us, backward 4710 -> 2250 us; bfloat16, no edge features, both: 6290 -> 2790 us; 4,000
-// events, 10 slots: backward 321 -> 226 us; 600 events, 172 edge features: forward 93 -> 55 us.
+// forward 3340 -> 1256 us, backward 4710 -> 2058 us; bfloat16, no edge features, both: 6290 -> 2378 us; 4,000
+// events, 10 slots: backward 321 -> 213 us; 600 events, 172 edge features: forward 93 -> 57 us.
 #include <algorithm>
 
 #include "gemm.h"
@@ -190,6 +190,15 @@ __device__ __forceinline__ void st4(float* p, float4 v) { *(float4*)p = v; }
 __device__ __forceinline__ void st2(float* p, float2 v) { *(float2*)p = v; }
 __device__ __forceinline__ void st2(uint16_t* p, float2 v) {   // values that are bfloat16 already
   *(uint32_t*)p = (__float_as_uint(v.x) >> 16) | (__float_as_uint(v.y) & 0xffff0000u);
+}
+
+// Slot rows that another kernel reads later: past the caches, which the gathered rows and weights keep.  60,000
+// events, 20 slots: forward 1312 -> 1256 us; bfloat16, both directions, 2407 -> 2378 us.
+__device__ __forceinline__ void st2_stream(float* p, float2 v) {
+  __builtin_nontemporal_store(f32x2_t{v.x, v.y}, (f32x2_t*)p);
+}
+__device__ __forceinline__ void st2_stream(uint16_t* p, float2 v) {   // values that are bfloat16 already
+  __builtin_nontemporal_store((__float_as_uint(v.x) >> 16) | (__float_as_uint(v.y) & 0xffff0000u), (uint32_t*)p);
 }
 
 // ---------------------------------------------------------------- packed products
@@ -500,7 +509,7 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
       if (j < cnt) {
 #pragma unroll
         for (int i = 0; i < XG; ++i)
-          if (2 * lane + 128 * i < dmx) st2(xs + (int64_t)j * dmx + 128 * i, x[p][i]);
+          if (2 * lane + 128 * i < dmx) st2_stream(xs + (int64_t)j * dmx + 128 * i, x[p][i]);
       }
       float v[H];
 #pragma unroll
@@ -795,7 +804,7 @@ __device__ __forceinline__ void bwd_slots(const BwdArgs& a, int64_t q, int cnt, 
         axpy2(pj, vt[h], dph);
         axpy2(ds, ut[h], dph);
       }
-      if (om) st2(dx + (int64_t)j * a.dm, dxm);
+      if (om) st2_stream(dx + (int64_t)j * a.dm, dxm);
       // d/d arg cos = -sin (the sign goes into the block's sums)
       const float2 gv = make_float2(dph.x * sn.x, dph.y * sn.y);
       axpy2(delta, gv, gw);
