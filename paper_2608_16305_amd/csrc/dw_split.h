@@ -61,8 +61,9 @@ __device__ __forceinline__ void dw_shift(int fr, int lim, float (&v)[NT][8]) {
 // The block's waves take its rows 32 at a time in turn, operands straight from memory: lane (fr, fg) holds rows
 // 8 fg .. 8 fg + 7 of a step, each column of Y and X split into three bfloat16 parts, and a pair of tiles takes
 // six 16x16x32 products (bf16_split.h) where float32 instructions take eight of twice the time.  A group's
-// next rows are requested as soon as its parts are made.  G = 2: waves w, w + 2 take the column group w (the
-// caller passes each wave its own X), G = 1: all four share one.  A group's sums are added in wave order.
+// next rows are requested as soon as its parts are made.  G column groups (the caller passes each wave its
+// group's X): wave w works for group w % G, 4 / G waves share a group's steps and their sums are added in
+// wave order.
 // Matrix time and the operands' reads bound it about equally.  Against 16x16x4 float32 instructions: the
 // attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us, of 12,000 rows 46 -> 34 us.
 template <int NI, int NJ, int G, class Out, class Bias>
@@ -138,6 +139,20 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
       dw_load<NI, 1>(Y, ldy, rn, R, fr, ylim, y);
     }
   }
+  if constexpr (NW == 1) {
+#pragma unroll
+    for (int a = 0; a < NI; ++a) {
+#pragma unroll
+      for (int b = 0; b < NJ; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), acc[a][b][r]);
+      float v = cs[a];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (fg == 0 && grp == 0) bias(dw_col<NI>(a, fr), v);
+    }
+    return;
+  }
   // the waves' sums meet in LDS a tile row at a time (two buffers, so that one barrier a row is enough), and a
   // group's waves add and store its tiles in turn
   float* lsum = lds + 2 * 4 * 7 * 256;
@@ -168,7 +183,7 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
 
 constexpr int DW_LDS = 2 * 4 * 7 * 256 + 7 * 4 * 64;   // floats
 
-// The body for the tiles that n by m outputs take (n, m at most 112).
+// The body for the tiles that n by m outputs take (n and m at most 112; m at most 64 with G = 4).
 template <int G, class Out, class Bias>
 __device__ __forceinline__ void dw_split_any(int n, int m, const float* Y, int64_t ldy, int ylim, const float* X,
                                              int64_t ldx, int xlim, int64_t R, int64_t s0, int64_t s1, float* lds,
@@ -177,8 +192,9 @@ __device__ __forceinline__ void dw_split_any(int n, int m, const float* Y, int64
     dw_split<decltype(ni)::value, decltype(nj)::value, G>(Y, ldy, ylim, X, ldx, xlim, R, s0, s1, lds, out, bias);
   };
   auto cols = [&](auto ni) {
-    if (m <= 64) run(ni, std::integral_constant<int, 4>{});
-    else run(ni, std::integral_constant<int, 7>{});
+    if (m <= 32) run(ni, std::integral_constant<int, 2>{});
+    else if (m <= 64) run(ni, std::integral_constant<int, 4>{});
+    else if constexpr (G < 4) run(ni, std::integral_constant<int, 7>{});
   };
   if (n <= 32) cols(std::integral_constant<int, 2>{});
   else if (n <= 64) cols(std::integral_constant<int, 4>{});

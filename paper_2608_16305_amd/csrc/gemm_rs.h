@@ -522,6 +522,9 @@ __global__ __launch_bounds__(G_THREADS, 1) void k_dw_rs(const float* __restrict_
 // (dw_split.h).  Against float32 instructions over LDS-staged rows, each wave a quarter of the columns: the link
 // decoder's two products of 60,000 and 120,000 rows of 100 by 100 72 -> 42 us, the GRU's of 4,800 rows 24.1 ->
 // 21.9 us.
+// Blocks with fewer steps than waves: a quarter of the columns a wave, over every step (4,000 targets, one or two steps
+// a block: the second model's whole step 210 -> 207 us; at eight the GRU's 4,800 rows took 47.9 for 46.4 us).
+constexpr int DW_OS_SHARED = 4;
 template <class Site>   // the call site names the kernel symbol only
 __global__ __launch_bounds__(G_THREADS, 1) void k_dw_os(DwOsBatch b) {
   static_assert(G_THREADS == 256, "four waves");
@@ -544,7 +547,7 @@ __global__ __launch_bounds__(G_THREADS, 1) void k_dw_os(DwOsBatch b) {
   float* part = q.part + bi * (int64_t)q.nx * ldp;
   const auto run = [&](auto groups, int c0, int m, int width) {   // columns c0 .. c0 + m - 1 for this wave
     dw_split_any<decltype(groups)::value>(
-        q.nx, width, q.X, q.ldx, q.nx, q.Y + c0, q.ldy, m, rows, s0, s1, lds,
+        q.nx, width, q.X, q.ldx, q.nx, q.Y + c0, q.ldy, max(m, 4), rows, s0, s1, lds,
         [&](int i, int j, float v) {
           if (i < q.nx && j < m) part[i * ldp + c0 + j] = v;
         },
@@ -552,13 +555,15 @@ __global__ __launch_bounds__(G_THREADS, 1) void k_dw_os(DwOsBatch b) {
           if (i < q.nx) part[i * ldp + q.ny] = v;
         });
   };
-  if (q.ny <= 112) {
-    run(std::integral_constant<int, 1>{}, 0, q.ny, q.ny);
-  } else {
-    const int half = (q.ny / 4 + 1) / 2 * 4;   // the wider of the two, a multiple of four
-    const bool second = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1;
-    run(std::integral_constant<int, 2>{}, second ? half : 0, second ? q.ny - half : half, half);
-  }
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const auto grouped = [&](auto groups) {
+    constexpr int N = decltype(groups)::value;
+    const int width = (q.ny / 4 + N - 1) / N * 4, c0 = min(width * (wid % N), q.ny - 4);   // multiples of four
+    run(groups, c0, width * (wid % N) < q.ny ? min(width, q.ny - c0) : 0, width);
+  };
+  if (s1 - s0 < DW_OS_SHARED) grouped(std::integral_constant<int, 4>{});
+  else if (q.ny <= 112) grouped(std::integral_constant<int, 1>{});
+  else grouped(std::integral_constant<int, 2>{});
 }
 
 // Host side (gemm_rs.hip): dW[nx, ny] = X^T Y and db[nx] = column sums of X over R rows
