@@ -32,39 +32,33 @@ constexpr int TG_CHUNKS = 64;  // chunks of the time encoder's block partials (f
 
 // ---------------------------------------------------------------- time encoding
 
-// cos and sin of a time argument.  x / (2 pi) = p + e (p the rounded product, e its error and the low part
-// of 1 / (2 pi)); f = p - rint(p) is exact.  With h = 1/4 - |f + e|, cos(2 pi (f + e)) = sin(2 pi h), an odd
-// polynomial of degree 9 on a quarter turn, and sin(2 pi (f + e)) = sign(f) cos(2 pi h), an even one of degree
-// 10 in the same h^2 (least-squares fits, 5e-9 and 3e-10 absolute).  Measured against 64 bits over
-// |x| <= 2^20: the cosine 1.8e-7 at most, 2.2e-8 rms (a correctly rounded one: 1.5e-8 rms).  Larger arguments
-// are reduced with 1 / (2 pi) in three doubles.  A third of the library cosine's instructions and a fraction
-// of its registers: the slots evaluate one per time column, the largest share of their loop.
+// cos and sin of a time argument.  n = rint(2 x / pi) and r = x - n pi / 2, pi / 2 as two floats: n and x up to
+// 2^20 make x - n PIO2_HI a multiple of 2^-23 below 1 (of 2^-24 for |x| < 1), so that product and difference are
+// exact, and the second product rounds r once; rlo is that rounding's error.  On |r| <= pi / 4 + 0.04 (the
+// rounding of 2 x / pi moves n near its midpoints), sin r = r + r s P(s) and cos r = 1 + s Q(s) with s = r r (own
+// minimax fits, 5e-9 and 4e-9 absolute), and n's two low bits choose between them and the sign.  Measured against
+// 64 bits over |x| <= 2^20: 7.1e-8 at most and 1.57e-8 rms, cosine and sine (the library's: 7.2e-8 and 1.80e-8;
+// without rlo, as the bfloat16 mode takes it, whose cosines are rounded again: 7.3e-8 and 1.71e-8).
+// Larger arguments are reduced with 1 / (2 pi) in three doubles.  The library's functions keep that reduction's
+// registers in every loop that calls them: the slots evaluate one cosine per time column.
 constexpr float ENC_MAX = 1048576.f;
-constexpr float INV_2PI_HI = 0.15915493667125702f, INV_2PI_LO = 6.4206382432985265e-09f;
+constexpr float PIO2_INV = 0.636619747f, PIO2_HI = 1.57079637f, PIO2_LO = -4.37113883e-08f;
+constexpr float ROUND_F = 12582912.f;              // 1.5 2^23: adding it rounds to a whole number, in the low bits
+constexpr double ROUND_D = 6755399441055744.;      // 1.5 2^52
 
-__device__ __forceinline__ float sin_turn(float h) {   // sin(2 pi h), |h| <= 1/4
-  const float s = h * h;
-  float p = fmaf(s, 39.682708740234375f, -76.57188415527344f);
-  p = fmaf(s, p, 81.60215759277344f);
-  p = fmaf(s, p, -41.341678619384766f);
-  return fmaf(h, 6.2831854820251465f, h * fmaf(s, p, -1.7484555314695172e-07f));
-}
-__device__ __forceinline__ float cos_turn(float h) {   // cos(2 pi h), |h| <= 1/4
-  const float s = h * h;
-  float p = fmaf(s, -25.006803512573242f, 60.1482048034668f);
-  p = fmaf(s, p, -85.4538345336914f);
-  p = fmaf(s, p, 64.9393539428711f);
-  p = fmaf(s, p, -19.739208221435547f);
-  return fmaf(s, p, 1.f);
-}
-__device__ __forceinline__ void turn(float x, float& f, float& e) {
+struct Quarter {   // x = n pi / 2 + r + rlo
+  float r, rlo;
+  uint32_t n;   // the low bits count
+};
+__device__ __forceinline__ Quarter quarter(float x) {
 #pragma clang fp contract(off)
-  const float p = x * INV_2PI_HI;   // f below must be of this rounded product, not fused into the subtraction
-  e = fmaf(x, INV_2PI_LO, fmaf(x, INV_2PI_HI, -p));
-  f = p - rintf(p);
+  const float m = fmaf(x, PIO2_INV, ROUND_F), n = m - ROUND_F;
+  const float d = fmaf(n, -PIO2_HI, x), r = fmaf(n, -PIO2_LO, d);
+  return Quarter{r, fmaf(n, -PIO2_LO, d - r), __float_as_uint(m)};
 }
 constexpr double INV_2PI_1 = 0.15915494309189535, INV_2PI_2 = -9.839338337591243e-18, INV_2PI_3 = -5.360718141446502e-34;
-// The same turn of any finite x: every product's fraction (and its rounding error's) summed.
+// x / (2 pi) less the nearest whole number, for any finite x: every product's fraction (and its rounding error's)
+// summed.
 __device__ __forceinline__ double turn_wide(float x) {
 #pragma clang fp contract(off)
   const double xd = x;
@@ -74,10 +68,24 @@ __device__ __forceinline__ double turn_wide(float x) {
   const double s = (p1 - rint(p1)) + ((r1 - rint(r1)) + ((p2 - rint(p2)) + ((r2 - rint(r2)) + (p3 - rint(p3)))));
   return s - rint(s);
 }
-__device__ __forceinline__ void turn_far(float x, float& f, float& e) {
-  const double s = turn_wide(x);
-  f = (float)s;
-  e = (float)(s - (double)f);
+__device__ __forceinline__ Quarter quarter_far(float x) {
+#pragma clang fp contract(off)
+  const double t = 4. * turn_wide(x), m = t + ROUND_D, r = (t - (m - ROUND_D)) * 1.570796326794896619231;
+  return Quarter{(float)r, (float)(r - (double)(float)r), (uint32_t)__double2loint(m)};
+}
+__device__ __forceinline__ float flip_sign(float v, uint32_t bit31) {
+  return __uint_as_float(__float_as_uint(v) ^ (bit31 & 0x80000000u));
+}
+template <bool SIN, bool LO>
+__device__ __forceinline__ void cos_sin(const Quarter& q, float& c, float& s) {
+  const float z = q.r * q.r;
+  const float P = fmaf(z, fmaf(z, -0.000194556327f, 0.00833164621f), -0.166666448f);
+  const float Q = fmaf(z, fmaf(z, fmaf(z, 2.43428403e-05f, -0.00138862419f), 0.0416666046f), -0.5f);
+  const float ys = LO ? q.r + fmaf(q.r * z, P, q.rlo) : fmaf(q.r * z, P, q.r);
+  const float yc = LO ? 1.f + fmaf(z, Q, -(q.r * q.rlo)) : fmaf(z, Q, 1.f);
+  const bool odd = q.n & 1u;
+  c = flip_sign(odd ? ys : yc, (q.n << 30) + 0x40000000u);   // n = 1, 2: negative
+  if (SIN) s = flip_sign(odd ? yc : ys, q.n << 30);          // n = 2, 3
 }
 // The correctly rounded cosine that a rounding to bfloat16 is decided on near its midpoints (see
 // cos_for_bf16): the Taylor series of sin on a quarter turn in double (3e-16).
@@ -98,17 +106,13 @@ __device__ __forceinline__ float wide_cos(float arg) {
 template <bool BF, bool SIN>
 __device__ __forceinline__ void encode(float2 w, float2 b, float delta, float2& c, float2& s) {
   const float a0 = time_arg(w.x, delta, b.x), a1 = time_arg(w.y, delta, b.y);
-  float f0, e0, f1, e1;
-  turn(a0, f0, e0);
-  turn(a1, f1, e1);
+  Quarter q0 = quarter(a0), q1 = quarter(a1);
   if (fmaxf(fabsf(a0), fabsf(a1)) > ENC_MAX) {
-    turn_far(a0, f0, e0);
-    turn_far(a1, f1, e1);
+    q0 = quarter_far(a0);
+    q1 = quarter_far(a1);
   }
-  const float g0 = copysignf(1.f, f0), g1 = copysignf(1.f, f1);
-  const float h0 = fmaf(-g0, e0, 0.25f - fabsf(f0)), h1 = fmaf(-g1, e1, 0.25f - fabsf(f1));
-  c = make_float2(sin_turn(h0), sin_turn(h1));
-  if (SIN) s = make_float2(g0 * cos_turn(h0), g1 * cos_turn(h1));
+  cos_sin<SIN, !BF>(q0, c.x, s.x);
+  cos_sin<SIN, !BF>(q1, c.y, s.y);
   if constexpr (BF) {
     auto near_tie = [](float y) {
       const int low = (int)(__float_as_uint(y) & 0xFFFFu) - 0x8000;
