@@ -452,10 +452,7 @@ __device__ __forceinline__ void load_x(const FwdArgs& a, int64_t nb, int64_t e, 
   }
 }
 
-// exp2 of a softmax argument (at most 2^16; the hardware's, 1 ulp).
-__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
-constexpr float LOG2E = 1.44269504088896340736f;
-constexpr float SOFTMAX_SLACK = 16.f;   // a score may exceed the reference by this much before it moves
+constexpr float SOFTMAX_SLACK = 11.f;   // a score may exceed the reference by this much before it moves
 
 // a / b with its rounding error taken out (b finite and positive).
 __device__ __forceinline__ float div_by(float a, float b, float inv) {
@@ -465,7 +462,7 @@ __device__ __forceinline__ float div_by(float a, float b, float inv) {
 
 // One query's slots: scores, softmax and the weighted row sums c.  Lane l holds two columns of each 128 of
 // the stored row and columns 2 l, 2 l + 1 of the time part, so a slot's index, time and probabilities are
-// scalars and its loads whole rows.  Half-wave h keeps head h's softmax, in powers of two.  CH slots are
+// scalars and its loads whole rows.  Half-wave h keeps head h's softmax.  CH slots are
 // loaded together; the softmax reference is the first slots' maximum and moves only when a score exceeds it
 // by SOFTMAX_SLACK, so a row is read once and the sums are rarely rescaled.  Two thirds of the loop's
 // instructions are the encoding and the dot products, which the vector unit bounds; the sums' loads
@@ -480,7 +477,7 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
   const int ct = ot ? 2 * lane : 0;
   const float2 tw = *(const float2*)(a.tw + ct), tb = *(const float2*)(a.tb + ct);
   T* xs = (T*)a.xs + q * a.k * dmx + 2 * lane;
-  const float scale = LOG2E / sqrtf((float)a.dh);
+  const float scale = 1.0f / sqrtf((float)a.dh);
   const float my_d = tau - my_t;
   float2 ux[H][XG], ut[H], sx[H][XG], st[H];
 #pragma unroll
@@ -533,7 +530,7 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
     if (j0 == 0) {
       mx = m;
     } else if (__any(m > mx + SOFTMAX_SLACK)) {   // rare
-      const float mn = fmaxf(m, mx), al = ex2(mx - mn);
+      const float mn = fmaxf(m, mx), al = expf(mx - mn);
       mx = mn;
       den *= al;
 #pragma unroll
@@ -550,7 +547,7 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
     float bd = 0.f;
 #pragma unroll
     for (int p = 0; p < CH; ++p) {
-      const float e = ex2(s[p] - mx);   // 0 past the count
+      const float e = expf(s[p] - mx);   // 0 past the count
       (BF ? bd : den) += e;
 #pragma unroll
       for (int h = 0; h < H; ++h) {
@@ -582,8 +579,8 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
   const float inv = 1.f / den;
   if (H == 2 || lane < 32) {
     float* P = a.p + (q * H + head) * a.k;
-    if (hl < a.k) P[hl] = hl < cnt ? ex2(my_s0 - mx) / den : 0.f;
-    if (hl + 32 < a.k) P[hl + 32] = hl + 32 < cnt ? ex2(my_s1 - mx) / den : 0.f;
+    if (hl < a.k) P[hl] = hl < cnt ? expf(my_s0 - mx) / den : 0.f;
+    if (hl + 32 < a.k) P[hl + 32] = hl + 32 < cnt ? expf(my_s1 - mx) / den : 0.f;
   }
 #pragma unroll
   for (int h = 0; h < H; ++h) {

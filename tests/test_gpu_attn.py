@@ -226,3 +226,35 @@ def test_time_encoding_error(span):
         log(f"  {name}: largest {np.abs(e).max():.2e}, rms {np.sqrt((e ** 2).mean()):.2e}")
     assert max(np.abs(e).max() for e in errs) <= 7.5e-8
     assert max(np.sqrt((e ** 2).mean()) for e in errs) <= 1.8e-8
+
+
+def _scored(scores, values, k):
+    """Queries whose slot j of row i has the score scores[i, j] and the value values[i, j] in the first head's first
+    column, all exact: u is one memory column (the score times 8, head width 64), the value another.  The
+    arguments of _forward_backward up to the times."""
+    Q, dm, dt, da = scores.shape[0], 4, 4, 128
+    p = _passing(dm, dt, da)
+    p["b_q"][0] = 1.0
+    p["W_k"][0, 0] = 16.0
+    p["W_v"][0, 1] = 1.0
+    mem = torch.zeros(Q * k, dm)
+    mem[:, 0], mem[:, 1] = scores.reshape(-1) / 2, values.reshape(-1)
+    i32 = dict(dtype=torch.int32)
+    return (p, mem, None, torch.zeros(Q, **i32), torch.zeros(Q), torch.arange(Q * k, **i32).view(Q, k), torch.zeros(Q, k),
+            torch.zeros(Q, k, **i32), torch.zeros(dt), torch.zeros(dt))
+
+
+def test_softmax_error():
+    """A probability between 0.5 and e^-15 against 64 bits: the exponential's (at most 1.4 ulp, 8.3e-8), the
+    denominator's and the quotient's rounding (6e-8 each), 2.1e-7 in all."""
+    Q = 3000
+    rng = np.random.default_rng(2)
+    scores = torch.zeros(Q, 2)
+    scores[:, 1] = torch.from_numpy(-rng.uniform(0, 15, Q).astype(np.float32))
+    values = torch.zeros(Q, 2)
+    values[:, 1] = 1.0
+    z, _, _ = _forward_backward(*_scored(scores, values, 2), torch.zeros(Q, 128), 2, 2, torch.zeros(1, dtype=torch.int32))
+    want = 1.0 / (1.0 + torch.exp(-scores[:, 1].double()))
+    err = ((z[:, 0].double() - want) / want).abs().max().item()
+    log(f"[attn] softmax: largest relative error {err:.2e}")
+    assert err <= 2.1e-7
