@@ -2,7 +2,8 @@
 //
 // x = hi + mid + lo, each the nearest bfloat16 of what is left: 24 significant bits, so a product with
 // bfloat16 weights is three exact products, and one of two float32 operands is six (the three smallest,
-// below 2^-26 of the whole, are left out).  A 16x16x32 instruction takes a sixteenth of the time that
+// below 2^-26 of the whole, are left out).  Below 2^-109 the low part loses bits (the smallest bfloat16 is 2^-133).
+// A 16x16x32 instruction takes a sixteenth of the time that
 // 16x16x4 float32 ones take for as many products, and rounds its float32 sum once per 32 of them instead
 // of once per product.
 #pragma once
@@ -24,8 +25,7 @@ __device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {
 }
 __device__ __forceinline__ float lo_bf16(uint32_t p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float hi_bf16(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
-// x less its bfloat16 part; an infinite part leaves a finite rest (the largest a finite x can have).
-__device__ __forceinline__ float rest_bf16(float x, float part) { return fmaxf(x - part, -6.646139978924579e35f); }
+constexpr float BF16_MAX = 3.3895313892515355e38f;
 
 // The parts of eight floats (operands of one 16x16x32 instruction).  No arrays of vectors, which the compiler
 // keeps in scratch memory.
@@ -38,14 +38,20 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(uint32_t a, uint32_t b, uint32_t c
 __device__ __forceinline__ bf16x8_t round8_bf16(const float (&x)[8]) {   // values that are bfloat16 already: exact
   return as_bf16x8(cvt2_bf16(x[0], x[1]), cvt2_bf16(x[2], x[3]), cvt2_bf16(x[4], x[5]), cvt2_bf16(x[6], x[7]));
 }
+// ENDS: also for the ends of the range.  A finite x past the largest bfloat16 has that one as its high part; an
+// infinite x has it too and an infinite middle part, and a finite low one, so that products with finite
+// bfloat16 weights are what x's own would be.  Without: such an x gives infinite or NaN parts.
+template <bool ENDS>
 __device__ __forceinline__ Bf16Parts split_bf16(const float (&x)[8]) {
+  auto high = [](float v) { return ENDS ? __builtin_amdgcn_fmed3f(v, -BF16_MAX, BF16_MAX) : v; };
+  auto low = [](float v) { return ENDS ? __builtin_amdgcn_fmed3f(v, -1e34f, 1e34f) : v; };   // (at most 6e33; NaN: -1e34)
   uint32_t h[4], m[4], l[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    h[i] = cvt2_bf16(x[2 * i], x[2 * i + 1]);
-    const float a = rest_bf16(x[2 * i], lo_bf16(h[i])), b = rest_bf16(x[2 * i + 1], hi_bf16(h[i]));
+    h[i] = cvt2_bf16(high(x[2 * i]), high(x[2 * i + 1]));
+    const float a = x[2 * i] - lo_bf16(h[i]), b = x[2 * i + 1] - hi_bf16(h[i]);
     m[i] = cvt2_bf16(a, b);
-    l[i] = cvt2_bf16(a - lo_bf16(m[i]), b - hi_bf16(m[i]));
+    l[i] = cvt2_bf16(low(a - lo_bf16(m[i])), low(b - hi_bf16(m[i])));
   }
   return Bf16Parts{as_bf16x8(h[0], h[1], h[2], h[3]), as_bf16x8(m[0], m[1], m[2], m[3]),
                    as_bf16x8(l[0], l[1], l[2], l[3])};

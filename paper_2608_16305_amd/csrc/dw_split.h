@@ -58,12 +58,26 @@ __device__ __forceinline__ void dw_shift(int fr, int lim, float (&v)[NT][8]) {
   }
 }
 
+// One output's sum over rows [r0, r1) with float32 products, four sums in turn.
+__device__ __forceinline__ float dw_plain(const float* y, int64_t ldy, const float* x, int64_t ldx, int64_t r0,
+                                          int64_t r1) {
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t r = r0; r < r1; r += 4) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (r + e < r1) v[e] = fmaf(y[(r + e) * ldy], x[(r + e) * ldx], v[e]);
+  }
+  return (v[0] + v[1]) + (v[2] + v[3]);
+}
+
 // The block's waves take its rows 32 at a time in turn, operands straight from memory: lane (fr, fg) holds rows
 // 8 fg .. 8 fg + 7 of a step, each column of Y and X split into three bfloat16 parts, and a pair of tiles takes
 // six 16x16x32 products (bf16_split.h) where float32 instructions take eight of twice the time.  A group's
 // next rows are requested as soon as its parts are made.  G column groups (the caller passes each wave its
 // group's X): wave w works for group w % G, 4 / G waves share a group's steps and their sums are added in
 // wave order.
+// An operand past the largest bfloat16, or infinite, meets the others' zero parts (NaN): a lane that stores a sum
+// which is not finite goes over its sums again with float32 products.
 // Matrix time and the operands' reads bound it about equally.  Against 16x16x4 float32 instructions: the
 // attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us, of 12,000 rows 46 -> 34 us.
 template <int NI, int NJ, int G, class Out, class Bias>
@@ -73,6 +87,21 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = wid % G, mine = wid / G;
   const int fr = lane & 15, fg = lane >> 4;
+  float bad = 0.f;   // NaN once a stored sum is not finite
+  const auto store = [&](int i, int j, float v) {
+    bad = fmaf(v, 0.f, bad);
+    out(i, j, v);
+  };
+  // the lane's sums again, of every tile row and of columns b0, b0 + db, ..
+  const auto again = [&](int b0, int db) {
+    const int64_t r0 = 32 * s0, r1 = min(32 * s1, R);
+    for (int a = 0; a < NI; ++a)
+      for (int b = b0; b < NJ; b += db)
+        for (int r = 0; r < 4; ++r) {
+          const int i = dw_col<NI>(a, 4 * fg + r), j = dw_col<NJ>(b, fr);
+          if (i < ylim && j < xlim) out(i, j, dw_plain(Y + i, ldy, X + j, ldx, r0, r1));
+        }
+  };
   f32x4 acc[NI][NJ];
   float cs[NI];
 #pragma unroll
@@ -101,11 +130,11 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
     if (dw_ragged<NI>(ylim)) dw_shift<NI>(fr, ylim, y);
     Bf16Parts xp[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) xp[j] = split_bf16(x[j]);
+    for (int j = 0; j < NJ; ++j) xp[j] = split_bf16<false>(x[j]);
     dw_load<NJ, 0>(X, ldx, rn, R, fr, xlim, x);
     dw_load<NJ, 1>(X, ldx, rn, R, fr, xlim, x);
     auto tile = [&](int i) {
-      const Bf16Parts yp = split_bf16(y[i]);
+      const Bf16Parts yp = split_bf16<false>(y[i]);
       float c = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) c += y[i][e];
@@ -145,12 +174,13 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
 #pragma unroll
       for (int b = 0; b < NJ; ++b)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), acc[a][b][r]);
+        for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), acc[a][b][r]);
       float v = cs[a];
       v += __shfl_xor(v, 16, 64);
       v += __shfl_xor(v, 32, 64);
       if (fg == 0 && grp == 0) bias(dw_col<NI>(a, fr), v);
     }
+    if (bad != 0.f) again(0, 1);
     return;
   }
   // the waves' sums meet in LDS a tile row at a time (two buffers, so that one barrier a row is enough), and a
@@ -168,7 +198,7 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
 #pragma unroll
       for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + lane) * 4);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
+      for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
     }
     if (wid == 3) {   // the last wave: it has the fewest tiles; group 0's sums
       float v = lsum[a * 4 * 64 + lane];
@@ -179,6 +209,7 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
       if (fg == 0) bias(dw_col<NI>(a, fr), v);
     }
   }
+  if (bad != 0.f) again(mine, NW);
 }
 
 constexpr int DW_LDS = 2 * 4 * 7 * 256 + 7 * 4 * 64;   // floats

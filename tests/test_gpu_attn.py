@@ -228,6 +228,52 @@ def test_time_encoding_error(span):
     assert max(np.sqrt((e ** 2).mean()) for e in errs) <= 1.8e-8
 
 
+@pytest.mark.parametrize("H,dtype", [(2, "f32"), (4, "f32"), (2, "bf16")])   # four heads: the general path
+@pytest.mark.parametrize("Q", [3, 700, 20_000])
+@pytest.mark.parametrize("kind", ["both", "largest", "infinite"])
+def test_gradients_at_the_ends_of_the_range(H, dtype, Q, kind):
+    """Infinite and nearly infinite output gradients: W_2's and b_2's gradients (a1 = 0.5 everywhere), and b_1's where
+    W_2 does not turn them to NaN (0 times infinity), are the products float32 gives, infinite where it does and
+    finite where it does, and the others' columns are what they are without them."""
+    bf16 = dtype == "bf16"
+    dm, da, k = 4, 100, 1
+    big = float(np.finfo(np.float32).max)
+    ends = {"both": {3: math.inf, 20: -math.inf, 41: big, 97: -big}, "largest": {41: big, 97: -big},
+            "infinite": {20: -math.inf}}[kind]
+    log(f"[attn] gradients at the ends of the range: H {H} {dtype} queries {Q} {kind}")
+    rng = np.random.default_rng(H + Q)
+    p = {n: torch.zeros(*s) for n, s in dict(W_q=(da, 2 * dm), W_k=(da, 2 * dm), W_v=(da, 2 * dm), W_o=(da, da),
+                                             W_1=(da, da + dm), W_2=(da, da)).items()}
+    p.update({"b" + n[1:]: torch.zeros(da) for n in list(p)})
+    p["b_1"] += 0.5
+    if kind == "infinite":
+        p["W_2"] += 0.5
+    else:
+        p["W_2"].fill_diagonal_(0.5)
+    if bf16:
+        p = {n: v.bfloat16() if n[0] == "W" else v for n, v in p.items()}
+    dz = torch.from_numpy((rng.standard_normal((Q, da)) / Q).astype(np.float32))
+    for n, v in ends.items():
+        dz[:, n] = 0.0
+        dz[Q // 2, n] = v
+    mem = torch.zeros(3, dm, dtype=torch.bfloat16 if bf16 else torch.float32)
+    i32 = dict(dtype=torch.int32)
+    _, g, _ = _forward_backward(p, mem, None, torch.zeros(Q, **i32), torch.zeros(Q), torch.full((Q, k), -1, **i32),
+                                torch.zeros(Q, k), torch.zeros(Q, k, **i32), torch.zeros(dm), torch.zeros(dm), dz, H, k,
+                                torch.zeros(1, **i32), bf16)
+    want = dz.double().sum(0)
+    for name, slope in (("W_2", 0.5), ("b_2", 1.0)) + ((("b_1", 0.5),) if kind == "largest" else ()):
+        got, ref = g[name].double(), slope * want
+        for n in ends:
+            assert (got[n] == ref[n]).all(), (name, n, got[n], ref[n])
+        rest = [n for n in range(da) if n not in ends]
+        scale = slope * dz[:, rest].abs().double().sum(0)
+        err = ((got.view(da, -1) - ref[:, None])[rest] / scale[:, None]).abs().max().item()
+        assert err <= 1e-6, (name, err)
+    if kind == "infinite":
+        assert (g["b_1"] == -math.inf).all()
+
+
 def _scored(scores, values, k):
     """Queries whose slot j of row i has the score scores[i, j] and the value values[i, j] in the first head's first
     column, all exact: u is one memory column (the score times 8, head width 64), the value another.  The
