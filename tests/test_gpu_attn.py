@@ -276,15 +276,15 @@ def test_gradients_at_the_ends_of_the_range(H, dtype, Q, kind):
 
 def _scored(scores, values, k):
     """Queries whose slot j of row i has the score scores[i, j] and the value values[i, j] in the first head's first
-    column, all exact: u is one memory column (the score times 8, head width 64), the value another.  The
-    arguments of _forward_backward up to the times."""
+    column, all exact: u is one memory column's 2^100 (the score times 8 over it, head width 64; -inf: a product past
+    the range), the value another.  The arguments of _forward_backward up to the time encoder."""
     Q, dm, dt, da = scores.shape[0], 4, 4, 128
     p = _passing(dm, dt, da)
-    p["b_q"][0] = 1.0
-    p["W_k"][0, 0] = 16.0
+    p["b_q"][0] = p["W_k"][0, 0] = 2.0 ** 50
     p["W_v"][0, 1] = 1.0
     mem = torch.zeros(Q * k, dm)
-    mem[:, 0], mem[:, 1] = scores.reshape(-1) / 2, values.reshape(-1)
+    mem[:, 0] = torch.where(scores < -1e38, -(2.0 ** 40), scores * 2.0 ** -97).reshape(-1)
+    mem[:, 1] = values.reshape(-1)
     i32 = dict(dtype=torch.int32)
     return (p, mem, None, torch.zeros(Q, **i32), torch.zeros(Q), torch.arange(Q * k, **i32).view(Q, k), torch.zeros(Q, k),
             torch.zeros(Q, k, **i32), torch.zeros(dt), torch.zeros(dt))
@@ -304,3 +304,20 @@ def test_softmax_error():
     err = ((z[:, 0].double() - want) / want).abs().max().item()
     log(f"[attn] softmax: largest relative error {err:.2e}")
     assert err <= 2.1e-7
+
+
+@pytest.mark.parametrize("first", [1, 4, 5, 9])
+def test_scores_below_the_range(first):
+    """Leading slots whose score is -inf (a product past the float range) weigh nothing beside the others."""
+    k, Q = 12, 20
+    rng = np.random.default_rng(first)
+    scores = torch.from_numpy(rng.uniform(-2, 2, (Q, k)).astype(np.float32))
+    scores[:, :first] = -math.inf
+    values = torch.from_numpy(rng.uniform(-1, 1, (Q, k)).astype(np.float32))
+    z, g, d_mem = _forward_backward(*_scored(scores, values, k), torch.ones(Q, 128) / Q, 2, k,
+                                    torch.arange(Q * k, dtype=torch.int32))
+    w = torch.softmax(scores[:, first:].double(), 1)
+    err = rel_err(z[:, 0].numpy(), (w * values[:, first:].double()).sum(1).numpy())
+    log(f"[attn] {first} leading scores of -inf: error {err:.1e}")
+    assert err <= 1e-6
+    assert all(torch.isfinite(v).all() for v in g.values()) and torch.isfinite(d_mem).all()
