@@ -16,7 +16,8 @@ namespace mtgnn {
 struct ProjShape {
   int64_t Q, P, N;
   int dm, dt, de, dep, da, H, dh, dhp, dap, k, kvp, Dq, Dkv;
-  int us, as;   // LDS row strides (multiples of 4, odd in 16-byte groups): a row of H kvp (or da + dm), of dap
+  int us, uu, as;   // LDS row strides (multiples of 4, odd in 16-byte groups): a row of H kvp (or da + dm), of
+                    // H (dm + dt), of dap
   int esz;      // bytes of a stored slot-row element
   ProjShape(const mtgnn_dims* d, int64_t max_q);
 };

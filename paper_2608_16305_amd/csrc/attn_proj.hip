@@ -351,18 +351,19 @@ __device__ __forceinline__ void segment(const float* X, int ldx, const float* __
   else mma_segment<RT>(X, ldx, w, K, acc);
 }
 
-// Y = X W^T for `heads` heads of `tiles` 16-column tiles each (head h reads X + h xh); the block's waves
-// take the units in turn.  f(head, row, column in the head, value) for every element.
+// Y = X W^T for `heads` heads of `tiles` 16-column tiles each (head h reads X + h xh), without each head's tiles
+// lo .. lo + skip - 1; the block's waves take the units in turn.  f(head, row, column in the head, value) for
+// every element.
 template <typename T, int RT, int NP, class F>
 __device__ __forceinline__ void dense(const float* X, int ldx, int xh, const float* __restrict__ W, int K, int tiles,
-                                      int heads, F f) {
+                                      int heads, F f, int lo = 0, int skip = 0) {
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fg = lane >> 4;
-  const int unit = pk_unit<T>(K);
-  for (int u = wid; u < tiles * heads; u += PW) {
-    const int h = u >= tiles ? 1 : 0, t = u - h * tiles;
+  const int unit = pk_unit<T>(K), own = tiles - skip;
+  for (int u = wid; u < own * heads; u += PW) {
+    const int h = u >= own ? 1 : 0, t = u - h * own + (u - h * own >= lo ? skip : 0);
     Acc<RT> acc;
-    segment<T, RT, NP>(X + h * xh, ldx, W + (size_t)u * unit, K, acc);
+    segment<T, RT, NP>(X + h * xh, ldx, W + (size_t)(h * tiles + t) * unit, K, acc);
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
       const f32x4 y = acc.total[r];
@@ -544,36 +545,28 @@ __device__ __forceinline__ void fwd_slots(const FwdArgs& a, int64_t q, int cnt, 
     }
     // bfloat16: a batch's terms are added among themselves first (fewer roundings of the whole sum, and so fewer
     // stored values that round the other way)
-    float2 bx[BF ? H : 1][XG], bt[BF ? H : 1];
-    float bd = 0.f;
+    float e[CH], bd = 0.f;
 #pragma unroll
     for (int p = 0; p < CH; ++p) {
-      const float e = expf(s[p] - mx);   // 0 past the count
-      (BF ? bd : den) += e;
-#pragma unroll
-      for (int h = 0; h < H; ++h) {
-        const float eh = lane_value(e, 32 * h);
-        if constexpr (BF) {
-          if (p == 0) {
-            bt[h] = scale2(ph[p], eh);
-#pragma unroll
-            for (int i = 0; i < XG; ++i) bx[h][i] = scale2(x[p][i], eh);
-            continue;
-          }
-        }
-        axpy2(eh, ph[p], BF ? bt[BF ? h : 0] : st[h]);
-#pragma unroll
-        for (int i = 0; i < XG; ++i) axpy2(eh, x[p][i], BF ? bx[BF ? h : 0][i] : sx[h][i]);
-      }
+      e[p] = expf(s[p] - mx);   // 0 past the count
+      (BF ? bd : den) += e[p];
     }
-    if constexpr (BF) {
-      den += bd;
+    den += bd;
 #pragma unroll
-      for (int h = 0; h < H; ++h) {
-        axpy2(1.f, bt[h], st[h]);
+    for (int h = 0; h < H; ++h) {
+      float eh[CH];
 #pragma unroll
-        for (int i = 0; i < XG; ++i) axpy2(1.f, bx[h][i], sx[h][i]);
-      }
+      for (int p = 0; p < CH; ++p) eh[p] = lane_value(e[p], 32 * h);
+      const auto add = [&](float2& sum, auto term) {
+        float2 t = BF ? scale2(term(0), eh[0]) : sum;
+#pragma unroll
+        for (int p = BF ? 1 : 0; p < CH; ++p) axpy2(eh[p], term(p), t);
+        if constexpr (BF) axpy2(1.f, t, sum);
+        else sum = t;
+      };
+      add(st[h], [&](int p) { return ph[p]; });
+#pragma unroll
+      for (int i = 0; i < XG; ++i) add(sx[h][i], [&](int p) { return x[p][i]; });
     }
   }
   if (cnt == 0) den = 1.f;   // the sums are zero
@@ -620,13 +613,24 @@ __device__ __forceinline__ void load_h(const FwdArgs& a, int64_t r0, int64_t M, 
   }
 }
 
+// Waves per SIMD: two blocks a CU (128 registers), except for two heads and three column groups, whose loops need
+// more.  With one block a CU, 60,000 queries of width 100, 10 slots, 100 edge features: bfloat16 forward 777 -> 501 us
+// with two.
+constexpr int two_blocks(int H, int XG) { return H == 2 && XG == 3 ? 2 : 4; }
+// Slots loaded together: what the registers of two blocks a CU leave.
+template <typename T>
+constexpr int fwd_chunk(int H, int XG) {
+  if (XG == 1) return 4;
+  return sizeof(T) == 2 && H + XG == 4 ? 1 : 2;
+}
+
 // A block of 16 RT queries.  LDS: U (rows of us) holds the query rows M[q], then u, then c, then [o | M[q]];
 // A (rows of as) the padded heads of qv, then the attention output, then a1.
 template <typename T, int H, int XG, bool ED, int RT>
-__global__ __launch_bounds__(PT, XG > 1 ? 2 : 4) void k_proj_fwd(FwdArgs a) {
+__global__ __launch_bounds__(PT, two_blocks(H, XG)) void k_proj_fwd(FwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   constexpr bool BF = sizeof(T) == 2;
-  constexpr int RB = 16 * RT, RW = RB / PW, CH = XG == 1 ? 4 : 2;
+  constexpr int RB = 16 * RT, RW = RB / PW, CH = fwd_chunk<T>(H, XG);
   __shared__ int s_cnt[RB];
   float* U = lds;
   float* A = lds + RB * a.us;
@@ -718,7 +722,7 @@ struct BwdArgs {
   const int32_t *nbr, *n_q;
   const float *q_t, *nt, *dz, *tw, *tb;
   int64_t max_q;
-  int dm, dt, dep, da, dh, dhp, dap, k, kvp, us, as;
+  int dm, dt, dep, da, dh, dhp, dap, k, kvp, us, uu, as;
   bool dz_copy;
   const float *w2t, *w1ot, *w1ht, *wot, *wvt, *wkt, *wk, *wqt;
   const float *qv, *c, *p, *a1;
@@ -727,8 +731,8 @@ struct BwdArgs {
 };
 
 // One query's slots, in the forward's lane layout: dx of the memory columns, du and the time encoder's
-// gradient sums.  D: the query's row of dc in LDS, overwritten with du; U: its row of u.  gw, gb: the sums
-// of this lane's time columns.
+// gradient sums.  D: the query's row of dc in LDS, overwritten with du; U: its row of u, per head the memory
+// columns, then the time columns.  gw, gb: the sums of this lane's time columns.
 template <typename T, int H, int XG, int CH>
 __device__ __forceinline__ void bwd_slots(const BwdArgs& a, int64_t q, int cnt, float my_t, float tau, float* D,
                                           const float* U, float2& gw, float2& gb) {
@@ -751,11 +755,11 @@ __device__ __forceinline__ void bwd_slots(const BwdArgs& a, int64_t q, int cnt, 
     float v[H];
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-      const float* uh = U + h * a.kvp;
+      const float* uh = U + h * (a.dm + a.dt);
       const float* dh = D + h * a.kvp;
       const float* ch = a.c + (q * H + h) * (int64_t)a.kvp;
       um[h] = om ? *(const float2*)(uh + 2 * lane) : Z2;
-      ut[h] = ot ? *(const float2*)(uh + dmx + ct) : Z2;
+      ut[h] = ot ? *(const float2*)(uh + a.dm + ct) : Z2;
       vt[h] = ot ? *(const float2*)(dh + dmx + ct) : Z2;
       st[h] = Z2;
       v[h] = dot2(vt[h], *(const float2*)(ch + dmx + ct), 0.f);
@@ -833,18 +837,19 @@ __device__ __forceinline__ void bwd_slots(const BwdArgs& a, int64_t q, int cnt, 
   }
 }
 
-// A block of 16 queries.  LDS: UD (rows of us) holds do, then dc, then du; UU dz, then u, then the waves'
-// time-encoder sums; A1 dattn, then dqv; A2 qv; D1 dm1 (rows of as).
+// A block of 16 queries.  LDS: UD (rows of us) holds dz, then do, then dc, then du; UU (rows of uu) u, whose edge
+// columns nothing reads, then the waves' time-encoder sums; A1 qv, then dattn, then dqv; D1 dm1 (rows of as).
+// Two blocks fit a CU up to about 330 columns a head.  With all of u's columns and a buffer each for dz and qv they
+// did up to about 250: 60,000 queries of width 64, 172 edge features, 2 heads, 4 and 10 slots 710 -> 515 and 805 -> 588 us.
 template <typename T, int H, int XG>
-__global__ __launch_bounds__(PT, XG > 1 ? 2 : 4) void k_proj_bwd(BwdArgs a) {
+__global__ __launch_bounds__(PT, two_blocks(H, XG)) void k_proj_bwd(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   constexpr int RB = 16, RW = RB / PW, CH = XG == 1 ? 4 : 2;
   __shared__ int s_cnt[RB];
   float* UD = lds;
   float* UU = UD + RB * a.us;
-  float* A1 = UU + RB * a.us;
-  float* A2 = A1 + RB * a.as;
-  float* D1 = A2 + RB * a.as;
+  float* A1 = UU + RB * a.uu;
+  float* D1 = A1 + RB * a.as;
   const int64_t M = eff_count(a.max_q, a.n_q);
   const int64_t r0 = (int64_t)blockIdx.x * RB;
   if (r0 >= M) return;   // block-uniform
@@ -862,15 +867,24 @@ __global__ __launch_bounds__(PT, XG > 1 ? 2 : 4) void k_proj_bwd(BwdArgs a) {
       v = a.dz[(r0 + r) * a.da + n];
       if (a.dz_copy) a.dzc[(r0 + r) * a.da + n] = v;
     }
-    UU[r * a.as + n] = v;
+    UD[r * a.us + n] = v;
   }
   for (int e = threadIdx.x; e < RB * (a.dap >> 2); e += PT) {
     const int r = e / (a.dap >> 2), g = e - r * (a.dap >> 2);
-    st4(A2 + r * a.as + 4 * g, r0 + r < M ? *(const float4*)(a.qv + (r0 + r) * a.dap + 4 * g) : Z4);
+    st4(A1 + r * a.as + 4 * g, r0 + r < M ? *(const float4*)(a.qv + (r0 + r) * a.dap + 4 * g) : Z4);
   }
   __syncthreads();
+  // u_h = W_k,h^T q_h, without the tiles that hold edge columns only
+  const int lo = tiles16(a.dm), skip = max(0, (a.dm + a.dep) / 16 - lo);
+  dense<T, 1, 3>(
+      A1, a.as, a.dhp, a.wkt, a.dhp, tiles16(a.kvp), H,
+      [&](int h, int r, int n, float v) {
+        const int c = n < a.dm ? n : n - a.dep;
+        if (n < a.kvp && (n < a.dm || c >= a.dm)) UU[r * a.uu + h * (a.dm + a.dt) + c] = v;
+      },
+      lo, skip);
   // dm1 = (W_2^T dz) [a1 > 0]
-  dense<T, 1, 3>(UU, a.as, 0, a.w2t, a.da, tiles16(a.da), 1, [&](int, int r, int n, float v) {
+  dense<T, 1, 3>(UD, a.us, 0, a.w2t, a.da, tiles16(a.da), 1, [&](int, int r, int n, float v) {
     if (n >= a.da) return;
     const bool ok = r0 + r < M;
     v = ok && a.a1[(min(r0 + r, M - 1)) * a.da + n] > 0.f ? v : 0.f;
@@ -893,12 +907,9 @@ __global__ __launch_bounds__(PT, XG > 1 ? 2 : 4) void k_proj_bwd(BwdArgs a) {
     A1[r * a.as + n] = v;
   });
   __syncthreads();
-  // dc_h = W_v,h^T dattn_h, u_h = W_k,h^T q_h
+  // dc_h = W_v,h^T dattn_h
   dense<T, 1, 3>(A1, a.as, a.dhp, a.wvt, a.dhp, tiles16(a.kvp), H, [&](int h, int r, int n, float v) {
     if (n < a.kvp) UD[r * a.us + h * a.kvp + n] = v;
-  });
-  dense<T, 1, 3>(A2, a.as, a.dhp, a.wkt, a.dhp, tiles16(a.kvp), H, [&](int h, int r, int n, float v) {
-    if (n < a.kvp) UU[r * a.us + h * a.kvp + n] = v;
   });
   __syncthreads();
   float2 gw = Z2, gb = Z2;
@@ -913,7 +924,7 @@ __global__ __launch_bounds__(PT, XG > 1 ? 2 : 4) void k_proj_bwd(BwdArgs a) {
     const int64_t q = r0 + r;
     const float nt = a.nt[q * a.k + min(lane, a.k - 1)], tau = a.q_t[q];
     const int cnt = __builtin_amdgcn_readlane(my_cnt, r);
-    bwd_slots<T, H, XG, CH>(a, q, cnt, nt, tau, UD + r * a.us, UU + r * a.us, gw, gb);
+    bwd_slots<T, H, XG, CH>(a, q, cnt, nt, tau, UD + r * a.us, UU + r * a.uu, gw, gb);
   }
   __syncthreads();
   {
@@ -1258,7 +1269,7 @@ int dw_problems(const ProjShape& s, DwProb* ps) {   // sizes only; the caller fi
 }
 
 size_t fwd_lds(const ProjShape& s, int rows) { return sizeof(float) * (size_t)rows * (s.us + s.as); }
-size_t bwd_lds(const ProjShape& s) { return sizeof(float) * 16 * (size_t)(2 * s.us + 3 * s.as); }
+size_t bwd_lds(const ProjShape& s) { return sizeof(float) * 16 * (size_t)(s.us + s.uu + 2 * s.as); }
 
 // Blocks of 32 queries (half the weight reads per query) from this many query rows on, where they still
 // fill the chip; of 16 below.
@@ -1331,6 +1342,7 @@ ProjShape::ProjShape(const mtgnn_dims* d, int64_t max_q) {
   Dq = dm + dt;
   Dkv = dm + de + dt;
   us = odd4(std::max(std::max(H * kvp, da + dm), 2 * dt));
+  uu = odd4(H * (dm + dt));
   as = odd4(std::max(dap, da));
   esz = d->dtype == MTGNN_F32 ? 4 : 2;
 }
@@ -1477,7 +1489,7 @@ mtgnn_status proj_bwd(const float* q_t, const int32_t* n_q, int64_t max_q, const
   a.q_t = q_t; a.nt = nt; a.dz = dz; a.tw = tw; a.tb = tb;
   a.max_q = max_q;
   a.dm = s.dm; a.dt = s.dt; a.dep = s.dep; a.da = s.da; a.dh = s.dh; a.dhp = s.dhp; a.dap = s.dap;
-  a.k = s.k; a.kvp = s.kvp; a.us = s.us; a.as = s.as;
+  a.k = s.k; a.kvp = s.kvp; a.us = s.us; a.uu = s.uu; a.as = s.as;
   a.dz_copy = ((uintptr_t)dz & 15) != 0;   // the weight gradients read 16-byte groups
   a.w2t = v.w[PK_W2T]; a.w1ot = v.w[PK_W1OT]; a.w1ht = v.w[PK_W1HT]; a.wot = v.w[PK_WOT]; a.wvt = v.w[PK_WVT];
   a.wkt = v.w[PK_WKT]; a.wk = v.w[PK_WK]; a.wqt = v.w[PK_WQT];

@@ -70,6 +70,12 @@ CASES = [(1, 4, 4, 0, 4, 1, 5, 5, "f32", False, 10.0),
          (2, 36, 100, 16, 20, 33, 48, 47, "f32", False, 1e4),
          (1, 32, 32, 2, 32, 5, 16_500, 16_400, "f32", True, 1e5),
          (2, 100, 100, 4, 100, 10, 16_400, 16_390, "f32", False, 1e5),
+         (2, 64, 64, 172, 64, 9, 50, 49, "f32", False, 1e5),
+         (2, 100, 100, 100, 100, 10, 33, 33, "f32", False, 1e5),
+         (2, 20, 12, 29, 36, 8, 40, 37, "f32", True, 1e4),        # edge columns inside one tile of 16
+         (1, 128, 128, 132, 128, 6, 33, 32, "bf16", False, 1e5),
+         (2, 100, 100, 101, 100, 10, 37, 36, "bf16", True, 1e5),
+         (2, 100, 100, 172, 100, 10, 20, 20, "bf16", False, 1e5),
          (2, 100, 100, 0, 100, 20, 50, 50, "bf16", False, 1e5),
          (1, 32, 32, 5, 32, 4, 35, 33, "bf16", True, 1e6),
          (4, 100, 100, 6, 100, 9, 45, 44, "f32", False, 1e4),      # general path: four heads
