@@ -1787,7 +1787,7 @@ mtgnn_status attn_bwd_impl(const int32_t* q_node, const float* q_t, const int32_
     // merge MLP: z = W_2 a1 + b_2, a1 = relu(m1), m1 = W_1 m_in + b_1
     // (their weight gradients run as one batch after the score backward)
     // output projection: o = W_o attn + b_o   (do = dm_in[:, :da])
-    if (merge_fused_ok(wt, da, dm)) {
+    if (merge_fused_ok(wt, da, dm) && ((uintptr_t)dz & 15) == 0) {   // reads 16-byte groups of dz
       MTGNN_TRY(merge_bwd_fused(dz, sv.merge_w, sv.m1, b.dm1, b.dm_in, b.dattn, n_q, max_q, da, dm, s));
     } else {
       MTGNN_TRY(linear_dx(dz, da, p->W_2, wt, da, b.dm1, da, Q, n_q, da, da, false, s, sv.m1, da));

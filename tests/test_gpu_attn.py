@@ -3,7 +3,7 @@
 Widths that are one and several column groups, padded heads (head width not a multiple of 4), padded and
 odd edge features, one and many slots (more than a half-wave's 32, a full wave's 64), 16- and 32-row blocks with
 ragged ends, queries without slots and with a gap in their slots, rows at unaligned addresses, time
-arguments past the fast range of the encoding, and dims that only the general path takes.
+arguments past the fast range of the encoding, and dims that the general path takes, each of its kernels.
 Gate: 1e-4 of each tensor's largest value in float32 (sums of at most a few hundred products: about
 1e-6), 2e-2 in bfloat16 (a stored value that rounds the other way moves by 2^-8).
 """
@@ -79,7 +79,20 @@ CASES = [(1, 4, 4, 0, 4, 1, 5, 5, "f32", False, 10.0),
          (2, 100, 100, 0, 100, 20, 50, 50, "bf16", False, 1e5),
          (1, 32, 32, 5, 32, 4, 35, 33, "bf16", True, 1e6),
          (4, 100, 100, 6, 100, 9, 45, 44, "f32", False, 1e4),      # general path: four heads
-         (2, 30, 14, 3, 22, 6, 40, 39, "f32", False, 1e3)]         # general path: odd widths
+         (2, 30, 14, 3, 22, 6, 40, 39, "f32", False, 1e3),         # odd widths
+         # the kernels for 16-byte groups: gather, key/value product and weight gradient of 200 columns by 200 and 216
+         # (one row tile and many), softmax of up to 10 and 20 slots
+         (4, 100, 100, 0, 100, 9, 45, 44, "f32", False, 1e4),
+         (4, 100, 100, 16, 100, 12, 45, 44, "f32", False, 1e4),
+         (4, 100, 100, 16, 100, 10, 3000, 2900, "f32", False, 1e4),
+         (4, 100, 100, 0, 100, 9, 45, 44, "bf16", False, 1e4),
+         (4, 100, 100, 16, 100, 10, 3000, 2900, "bf16", False, 1e4),
+         (4, 36, 20, 5, 48, 7, 45, 44, "bf16", True, 1e4),
+         (2, 100, 100, 260, 100, 20, 45, 44, "f32", False, 1e4),
+         (2, 100, 100, 260, 100, 9, 45, 44, "bf16", False, 1e4),
+         (1, 96, 100, 260, 100, 20, 45, 44, "f32", False, 1e4),
+         (1, 96, 100, 260, 100, 10, 45, 44, "f32", True, 1e4),
+         (1, 160, 100, 8, 128, 30, 45, 44, "f32", False, 1e4)]     # more than 20 slots, a head of 128
 
 
 @pytest.mark.parametrize("H,dm,dt,de,da,k,max_q,n_q,dtype,unaligned,span", CASES)
