@@ -225,6 +225,9 @@ mtgnn_status mtgnn_sample_recent(const int64_t* csr_off, const int32_t* csr_nbr,
  *   o     = W_o a + b_o
  *   z     = W_2 relu(W_1 [o || M[q_node]] + b_1) + b_2
  * phi(dt) = cos(time_w * dt + time_b) with the rounding of mtgnn_build_messages.
+ * Evaluated per query and head (scores against W_k^T q, values as W_v of the weighted row sum) where
+ * n_heads <= 2, d_mem, d_time and d_attn are multiples of 4 up to 128, d_time > 0 and d_edge <= 256; per
+ * neighbour slot at other widths.  The two round differently.
  *   nbr, nt, neid -- [max_q, k] as written by mtgnn_sample_recent;
  *   memory        -- the table after this step's mtgnn_gru_update;
  *   z             -- [max_q, d_attn] float32 out;
@@ -614,9 +617,18 @@ mtgnn_status mtgnn_build_temporal_csr(const int32_t* src, const int32_t* dst, co
 /* Launch timer (instrumentation for benchmarks; not part of the step).
  * mtgnn_timer_start arms it: each of the next `max_launches` launches whose
  * timer name equals `kernel` is bracketed by HIP events recorded on the
- * stream of that launch.  The names are the call-site names of the
- * matrix-product kernels ("gemm_kv_proj", "gemm_kv_dw", "gemm_kv_dx", "gemm")
- * and the function names of the other kernels (e.g. "k_attn_core").
+ * stream of that launch; a name that no launch carries gives 0 launches.
+ * The names that launches carry:
+ *   attention by per-query projected vectors (the widths that
+ *     mtgnn_temporal_attn names): "attn_fwd", "attn_bwd" (every data gradient),
+ *     "attn_dw" (every weight gradient);
+ *   attention at other widths: "gemm_kv_proj", "k_attn_core",
+ *     "k_attn_core_bwd", "gemm_kv_dw", "gemm_kv_dx" (the products over the
+ *     neighbour slots), "merge_fwd", "merge_bwd" (float32, fused widths);
+ *   memory update: "gru_fused" (float32, fused widths), "gemm_gru_dw";
+ *   loss: "link_fused" (the fused decoder's widths);
+ *   anywhere: "dw_os" (batched weight gradients), "gemm" (the other matrix
+ *     products).
  * mtgnn_timer_stop waits for the recorded events (host-blocking), returns
  * the summed duration in milliseconds and the number of timed launches, and
  * disarms the timer.  Host-side state: use from one host thread. */
