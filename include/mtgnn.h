@@ -226,8 +226,10 @@ mtgnn_status mtgnn_sample_recent(const int64_t* csr_off, const int32_t* csr_nbr,
  *   z     = W_2 relu(W_1 [o || M[q_node]] + b_1) + b_2
  * phi(dt) = cos(time_w * dt + time_b) with the rounding of mtgnn_build_messages.
  * Evaluated per query and head (scores against W_k^T q, values as W_v of the weighted row sum) where
- * n_heads <= 2, d_mem, d_time and d_attn are multiples of 4 up to 128, d_time > 0 and d_edge <= 256; per
- * neighbour slot at other widths.  The two round differently.
+ * n_heads <= 2, d_mem, d_time and d_attn are multiples of 4 up to 128, d_time > 0, d_edge <= 256 and, with
+ * r = d_mem + d_edge rounded up to a multiple of 4,
+ *   r <= 256 (one head) or r <= 128 (two), or k >= 2 and (one head or r <= 256), or k d_attn >= 400;
+ * per neighbour slot at other widths.  The two round differently.
  *   nbr, nt, neid -- [max_q, k] as written by mtgnn_sample_recent;
  *   memory        -- the table after this step's mtgnn_gru_update;
  *   z             -- [max_q, d_attn] float32 out;

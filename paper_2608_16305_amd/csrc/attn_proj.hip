@@ -1370,9 +1370,26 @@ ProjShape::ProjShape(const mtgnn_dims* d, int64_t max_q) {
   esz = d->dtype == MTGNN_F32 ? 4 : 2;
 }
 
+// The kernels' limits, then the cost: here a query costs its heads' projected vectors (a row of columns each, in
+// products and in LDS), on the general path a slot costs its key and value, 2 d_attn columns.  Measured times of
+// this path over the general one's, forward / backward (60,000 queries, a fifth without slots, two fifths with all k;
+// float32, 4-divisible widths, which suit the general path best):
+//   rows to 128, 2 heads, k 1: width 32 0.76 / 0.89, width 128 0.81 / 1.13
+//   rows to 256, 2 heads, k 1 and 2: width 64, 172 edge features 0.91 / 1.13 and 0.77 / 1.03, width 100, 64 edge
+//     features 1.11 / 1.06 and 0.99 / 0.93; 1 head, k 1: width 100, 100 edge features 0.83 / 0.98
+//   rows past 256, 1 head, k 1 and 2: width 32, 256 edge features 0.89 / 1.11 and 0.76 / 1.04
+//   rows past 256, 2 heads (one block a CU), 256 edge features: width 32, k 10 and 14 1.15 / 0.94 and 1.00 / 0.80;
+//     width 64, k 4 and 6 1.07 / 0.94 and 0.96 / 0.84; width 100, k 2 and 4 1.14 / 1.26 and 0.95 / 1.01; width 128, k 2
+//     and 4 1.00 / 1.03 and 0.82 / 0.81; bfloat16, width 100, k 4 0.93 / 0.85
+// The slots a batch really has are not known here: one without any takes 1.0 / 1.18 (width 100, k 10).
 bool proj_ok(const mtgnn_dims* d) {
-  return d->n_heads <= 2 && d->d_mem % 4 == 0 && d->d_time % 4 == 0 && d->d_attn % 4 == 0 && d->d_time > 0 &&
-         d->d_mem <= 128 && d->d_time <= 128 && d->d_attn <= 128 && d->d_edge <= 256 && d->k <= 64;
+  if (d->n_heads > 2 || d->d_mem % 4 != 0 || d->d_time % 4 != 0 || d->d_attn % 4 != 0 || d->d_time <= 0 ||
+      d->d_mem > 128 || d->d_time > 128 || d->d_attn > 128 || d->d_edge > 256 || d->k > 64)
+    return false;
+  const int row = d->d_mem + (d->d_edge + 3) / 4 * 4;
+  if (row <= (d->n_heads == 1 ? 256 : 128)) return true;
+  if (d->n_heads == 1 || row <= 256) return d->k >= 2;
+  return d->k * d->d_attn >= 400;
 }
 
 ProjSave carve_proj_save(void* base, const ProjShape& s) {

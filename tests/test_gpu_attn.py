@@ -92,7 +92,13 @@ CASES = [(1, 4, 4, 0, 4, 1, 5, 5, "f32", False, 10.0),
          (2, 100, 100, 260, 100, 9, 45, 44, "bf16", False, 1e4),
          (1, 96, 100, 260, 100, 20, 45, 44, "f32", False, 1e4),
          (1, 96, 100, 260, 100, 10, 45, 44, "f32", True, 1e4),
-         (1, 160, 100, 8, 128, 30, 45, 44, "f32", False, 1e4)]     # more than 20 slots, a head of 128
+         (1, 160, 100, 8, 128, 30, 45, 44, "f32", False, 1e4),     # more than 20 slots, a head of 128
+         # rows past 128 and 256 columns with few slots, to either side of the rule
+         (2, 100, 100, 172, 100, 3, 45, 44, "f32", False, 1e4),
+         (2, 100, 100, 172, 100, 4, 45, 44, "f32", False, 1e4),
+         (2, 100, 100, 64, 100, 1, 45, 44, "f32", False, 1e4),
+         (2, 100, 100, 64, 100, 2, 45, 44, "f32", False, 1e4),
+         (1, 128, 128, 190, 128, 1, 45, 44, "bf16", False, 1e4)]
 
 
 @pytest.mark.parametrize("H,dm,dt,de,da,k,max_q,n_q,dtype,unaligned,span", CASES)

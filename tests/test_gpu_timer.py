@@ -54,6 +54,10 @@ def test_header_lists_the_names():
 
 #        H  width edge k   by query
 ROUTES = [(2, 100, 16, 5, True), (1, 32, 0, 1, True),
+          (2, 128, 0, 1, True), (2, 128, 1, 1, False), (2, 128, 1, 2, True),       # rows to and past 128
+          (1, 128, 128, 1, True), (1, 128, 129, 1, False), (1, 128, 129, 2, True),   # to and past 256, one head
+          (2, 128, 128, 2, True), (2, 100, 157, 3, False), (2, 100, 157, 4, True),   # two heads: k d_attn >= 400
+          (2, 32, 256, 12, False), (2, 32, 256, 13, True),
           (4, 100, 16, 5, False), (2, 30, 0, 5, False), (1, 64, 257, 20, False)]
 
 
