@@ -326,7 +326,7 @@ __device__ __forceinline__ void mma_segment_bf16(const float* X, int ldx, const 
           const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
           const bf16x8_t wb = __builtin_bit_cast(bf16x8_t, b[i]);
           if constexpr (NP == 3) {
-            const Bf16Parts a = split_bf16<true>(x);
+            const Bf16Parts a = split_bf16(x);
             acc.v[r][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.lo, wb, acc.v[r][1], 0, 0, 0);
             acc.v[r][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, wb, acc.v[r][0], 0, 0, 0);
             acc.v[r][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.mid, wb, acc.v[r][1], 0, 0, 0);
@@ -996,7 +996,7 @@ struct DwArgs {
 };
 
 __global__ __launch_bounds__(256, 1) void k_proj_dw(DwArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[DW_LDS];
+  __shared__ __attribute__((aligned(16))) float lds[dw_lds(1)];
   int u = 0;
   while (u + 1 < a.n && (int)blockIdx.x >= a.u[u + 1].b_begin) ++u;
   const DwUnit q = a.u[u];

@@ -80,6 +80,12 @@ __device__ __forceinline__ float dw_plain(const float* y, int64_t ldy, const flo
 // which is not finite goes over its sums again with float32 products.
 // Matrix time and the operands' reads bound it about equally.  Against 16x16x4 float32 instructions: the
 // attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us, of 12,000 rows 46 -> 34 us.
+//
+// An instruction rounds its accumulator every eight products (16x16x4: every one), so a long sum's error is of those
+// roundings at its full size: a sum of DW_SEGMENT steps joins the total by one addition.  The attention's value
+// gradient over 60,000 rows against 64 bits: 1.4e-7 with one chain a block, 7.9e-8 with segments of 16, 5.6e-8 with 8
+// (float32 products over its 700,000 slots: 7.6e-8).  180,000 rows: backward 2058 us, 2081 with 16, 2116 with 8.
+constexpr int DW_SEGMENT = 8;
 template <int NI, int NJ, int G, class Out, class Bias>
 __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, const float* X, int64_t ldx, int xlim,
                                          int64_t R, int64_t s0, int64_t s1, float* lds, Out out, Bias bias) {
@@ -105,70 +111,73 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
   f32x4 acc[NI][NJ];
   float cs[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    cs[i] = 0.f;
+  for (int i = 0; i < NI; ++i) cs[i] = 0.f;
+  const auto steps = [&](int64_t begin, int64_t end) {   // the wave's steps of [begin, end), begin + mine the first
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float y[NI][8], x[NJ][8];
-  if (s0 + mine < s1) {
-    const int64_t r = 32 * (s0 + mine) + 8 * fg;
+  if (begin + mine < end) {
+    const int64_t r = 32 * (begin + mine) + 8 * fg;
     dw_load<NJ, 0>(X, ldx, r, R, fr, xlim, x);
     dw_load<NJ, 1>(X, ldx, r, R, fr, xlim, x);
     dw_load<NI, 0>(Y, ldy, r, R, fr, ylim, y);
     dw_load<NI, 1>(Y, ldy, r, R, fr, ylim, y);
   }
-  for (int64_t s = s0 + mine; s < s1; s += NW) {
-    const int64_t r = 32 * s + 8 * fg, rn = min(32 * (s + NW), R - 1) + 8 * fg;   // the next step's (in range) rows
-    if (32 * s + 32 > R) {   // the last, ragged step
-      dw_zero<NJ, 0>(r, R, x);
-      dw_zero<NJ, 1>(r, R, x);
-      dw_zero<NI, 0>(r, R, y);
-      dw_zero<NI, 1>(r, R, y);
+    for (int64_t s = begin + mine; s < end; s += NW) {
+      const int64_t r = 32 * s + 8 * fg, rn = min(32 * (s + NW), R - 1) + 8 * fg;   // the next step's (in range) rows
+      if (32 * s + 32 > R) {   // the last, ragged step
+        dw_zero<NJ, 0>(r, R, x);
+        dw_zero<NJ, 1>(r, R, x);
+        dw_zero<NI, 0>(r, R, y);
+        dw_zero<NI, 1>(r, R, y);
+      }
+      if (dw_ragged<NJ>(xlim)) dw_shift<NJ>(fr, xlim, x);
+      if (dw_ragged<NI>(ylim)) dw_shift<NI>(fr, ylim, y);
+      Bf16Right xp[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) xp[j] = split_right(x[j]);
+      dw_load<NJ, 0>(X, ldx, rn, R, fr, xlim, x);
+      dw_load<NJ, 1>(X, ldx, rn, R, fr, xlim, x);
+      auto tile = [&](int i) {
+        const Bf16Left yp = split_left(y[i]);
+        float c = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c += y[i][e];
+        cs[i] += c;
+        // the small products first; a pair of terms of all tiles before the next of one (the chains don't wait)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hm, xp[j].mm, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mh, xp[j].mm, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mh, xp[j].hl, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hm, xp[j].lh, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hl, xp[j].hh, acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.lh, xp[j].hh, acc[i][j], 0, 0, 0);
+      };
+#pragma unroll
+      for (int i = 0; i < (NI < 4 ? NI : 4); ++i) tile(i);
+      dw_load<NI, 0>(Y, ldy, rn, R, fr, ylim, y);
+      if constexpr (NI > 4) {
+#pragma unroll
+        for (int i = 4; i < NI; ++i) tile(i);
+        dw_load<NI, 1>(Y, ldy, rn, R, fr, ylim, y);
+      }
     }
-    if (dw_ragged<NJ>(xlim)) dw_shift<NJ>(fr, xlim, x);
-    if (dw_ragged<NI>(ylim)) dw_shift<NI>(fr, ylim, y);
-    Bf16Parts xp[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) xp[j] = split_bf16<false>(x[j]);
-    dw_load<NJ, 0>(X, ldx, rn, R, fr, xlim, x);
-    dw_load<NJ, 1>(X, ldx, rn, R, fr, xlim, x);
-    auto tile = [&](int i) {
-      const Bf16Parts yp = split_bf16<false>(y[i]);
-      float c = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) c += y[i][e];
-      cs[i] += c;
-      // the small products first; a term of all tiles before the next term of one (the chains don't wait)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.lo, xp[j].hi, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].lo, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mid, xp[j].mid, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.mid, xp[j].hi, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].mid, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yp.hi, xp[j].hi, acc[i][j], 0, 0, 0);
-    };
-#pragma unroll
-    for (int i = 0; i < (NI < 4 ? NI : 4); ++i) tile(i);
-    dw_load<NI, 0>(Y, ldy, rn, R, fr, ylim, y);
-    if constexpr (NI > 4) {
-#pragma unroll
-      for (int i = 4; i < NI; ++i) tile(i);
-      dw_load<NI, 1>(Y, ldy, rn, R, fr, ylim, y);
-    }
-  }
+  };
   if constexpr (NW == 1) {
+    steps(s0, s1);
 #pragma unroll
     for (int a = 0; a < NI; ++a) {
 #pragma unroll
@@ -183,36 +192,54 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
     if (bad != 0.f) again(0, 1);
     return;
   }
-  // the waves' sums meet in LDS a tile row at a time (two buffers, so that one barrier a row is enough), and a
-  // group's waves add and store its tiles in turn
-  float* lsum = lds + 2 * 4 * 7 * 256;
+  // The waves' sums meet in LDS a tile row at a time (two buffers, so that one barrier a row is enough; one where the
+  // totals leave no room), and a group's waves add its tiles in turn: every DW_SEGMENT steps of a wave to the
+  // totals of the steps before, in LDS too, and store them after the last.
+  constexpr int BUFS = G == 2 ? 1 : 2;
+  float* lsum = lds + BUFS * 4 * 7 * 256;
+  float* total = lsum + 7 * 4 * 64;
+#pragma unroll 1
+  for (int64_t begin = s0;; begin += NW * DW_SEGMENT) {
+    const bool last = begin + NW * DW_SEGMENT >= s1;
+    steps(begin, last ? s1 : begin + NW * DW_SEGMENT);
 #pragma unroll
-  for (int a = 0; a < NI; ++a) {
-    float* buf = lds + (a & 1) * 4 * 7 * 256;
+    for (int a = 0; a < NI; ++a) {
+      float* buf = lds + a % BUFS * 4 * 7 * 256;
 #pragma unroll
-    for (int b = 0; b < NJ; ++b) *(f32x4*)(buf + ((wid * NJ + b) * 64 + lane) * 4) = acc[a][b];
-    lsum[(a * 4 + wid) * 64 + lane] = cs[a];
-    __syncthreads();
-    for (int b = mine; b < NJ; b += NW) {
-      f32x4 v = *(const f32x4*)(buf + ((grp * NJ + b) * 64 + lane) * 4);
+      for (int b = 0; b < NJ; ++b) *(f32x4*)(buf + ((wid * NJ + b) * 64 + lane) * 4) = acc[a][b];
+      if (last) lsum[(a * 4 + wid) * 64 + lane] = cs[a];
+      __syncthreads();
+      for (int b = mine; b < NJ; b += NW) {
+        f32x4 v = *(const f32x4*)(buf + ((grp * NJ + b) * 64 + lane) * 4);
 #pragma unroll
-      for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + lane) * 4);
+        for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + lane) * 4);
+        f32x4* t = (f32x4*)(total + (((a * G + grp) * NJ + b) * 64 + lane) * 4);   // this lane's alone
+        if (begin > s0) v += *t;
+        if (last) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
+          for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
+        } else {
+          *t = v;
+        }
+      }
+      if (last && wid == 3) {   // the last wave: it has the fewest tiles; group 0's sums
+        float v = lsum[a * 4 * 64 + lane];
+#pragma unroll
+        for (int l = 1; l < NW; ++l) v += lsum[(a * 4 + G * l) * 64 + lane];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (fg == 0) bias(dw_col<NI>(a, fr), v);
+      }
+      if (BUFS == 1) __syncthreads();
     }
-    if (wid == 3) {   // the last wave: it has the fewest tiles; group 0's sums
-      float v = lsum[a * 4 * 64 + lane];
-#pragma unroll
-      for (int l = 1; l < NW; ++l) v += lsum[(a * 4 + G * l) * 64 + lane];
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
-      if (fg == 0) bias(dw_col<NI>(a, fr), v);
-    }
+    if (last) break;
+    __syncthreads();   // the buffers are free for the next segment
   }
   if (bad != 0.f) again(mine, NW);
 }
 
-constexpr int DW_LDS = 2 * 4 * 7 * 256 + 7 * 4 * 64;   // floats
+// Floats of LDS: buffers, the columns' sums and the totals (G column groups).
+constexpr int dw_lds(int G) { return (G == 2 ? 1 : 2) * 4 * 7 * 256 + 7 * 4 * 64 + G * 7 * 7 * 256; }
 
 // The body for the tiles that n by m outputs take (n and m at most 112; m at most 64 with G = 4).
 template <int G, class Out, class Bias>

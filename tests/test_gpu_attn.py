@@ -346,3 +346,28 @@ def test_scores_below_the_range(first):
     log(f"[attn] {first} leading scores of -inf: error {err:.1e}")
     assert err <= 1e-6
     assert all(torch.isfinite(v).all() for v in g.values()) and torch.isfinite(d_mem).all()
+
+
+@pytest.mark.parametrize("H", [2, 4])   # four heads: the general path
+@pytest.mark.parametrize("Q", [2_000, 60_000])
+def test_weight_gradient_of_columns_that_hardly_vary(H, Q):
+    """W_2's gradient where every row's a1 is the same and its dz column varies by a tenth: a long sum of nearly
+    equal terms, whose roundings must not all go one way.  Error of the whole against 64 bits (2-norm): the result's
+    own rounding 3.4e-8, the partial sums' that of a few float32 additions more; with roundings that do not
+    average out it grows past 2e-7."""
+    dm, da, k = 4, 100, 1
+    log(f"[attn] nearly constant columns: H {H} queries {Q}")
+    rng = np.random.default_rng(H + Q)
+    p = {n: torch.zeros(*s) for n, s in dict(W_q=(da, 2 * dm), W_k=(da, 2 * dm), W_v=(da, 2 * dm), W_o=(da, da),
+                                             W_1=(da, da + dm), W_2=(da, da)).items()}
+    p.update({"b" + n[1:]: torch.zeros(da) for n in list(p)})
+    p["b_1"] = torch.from_numpy(rng.uniform(0.5, 1.0, da).astype(np.float32))
+    dz = torch.from_numpy((rng.uniform(0.5, 1.0, da) * (1 + 0.1 * rng.standard_normal((Q, da))) / Q).astype(np.float32))
+    i32 = dict(dtype=torch.int32)
+    _, g, _ = _forward_backward(p, torch.zeros(3, dm), None, torch.zeros(Q, **i32), torch.zeros(Q),
+                                torch.full((Q, k), -1, **i32), torch.zeros(Q, k), torch.zeros(Q, k, **i32),
+                                torch.zeros(dm), torch.zeros(dm), dz, H, k, torch.zeros(1, **i32))
+    ref = torch.outer(dz.double().sum(0), p["b_1"].double())
+    err = ((g["W_2"].double() - ref).norm() / ref.norm()).item()
+    log(f"  error {err:.2e}")
+    assert err <= 1.0e-7
