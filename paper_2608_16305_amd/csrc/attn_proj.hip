@@ -296,9 +296,9 @@ __device__ __forceinline__ void mma_segment(const float* X, int ldx, const float
 
 // The same for bfloat16 weights, float32 rows as the sum of NP bfloat16 parts (1: rows that hold bfloat16
 // values).  K % 4 == 0: a lane's eight columns end on a group of four, and those past K count as zero.  The
-// products are exact and a chain rounds once per chunk: the float32 instructions round
-// once a product and take 16 (NP = 1) or 5 (NP = 3) times the matrix time.  60,000 events, 20 slots, both
-// directions: 2795 -> 2514 us.
+// products are exact and an instruction rounds once every eight of them: the float32 instructions round once a
+// product and take 16 (NP = 1) or 5 (NP = 3) times the matrix time.  60,000 events, 20 slots, both directions:
+// 2795 -> 2514 us.
 template <int RT, int NP>
 __device__ __forceinline__ void mma_segment_bf16(const float* X, int ldx, const float* __restrict__ w, int K,
                                                  Acc<RT>& acc) {
@@ -1038,10 +1038,10 @@ __global__ __launch_bounds__(256) void k_proj_dw_reduce(DwRed a) {
     const int64_t nb = cdiv(eff_count(a.max_q, a.n_q), 16);
     const int64_t b0 = nb * blockIdx.x / TG_CHUNKS, b1 = nb * (blockIdx.x + 1) / TG_CHUNKS;
     for (int j = threadIdx.x; j < a.dt2; j += 256) {
-      float v = 0.f;
+      double v = 0.;   // the sums grow with the rows, all of one sign in the slow columns
 #pragma unroll 8
       for (int64_t b = b0; b < b1; ++b) v += a.tg[b * a.dt2 + j];
-      a.tg2[(int64_t)blockIdx.x * a.dt2 + j] = v;
+      a.tg2[(int64_t)blockIdx.x * a.dt2 + j] = (float)v;
     }
     return;
   }
@@ -1097,10 +1097,15 @@ __global__ __launch_bounds__(256) void k_proj_time(const float* __restrict__ tg2
   __syncthreads();
   if (t < 64) {
     static_assert(TG_CHUNKS == 64, "one chunk per lane");
-    const float gw = wave_sum(tg2[t * 2 * dt + j]), gb = wave_sum(tg2[t * 2 * dt + dt + j]);
+    double gw = tg2[t * 2 * dt + j], gb = tg2[t * 2 * dt + dt + j];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      gw += __shfl_xor(gw, o, 64);
+      gb += __shfl_xor(gb, o, 64);
+    }
     if (t == 0) {
-      dw[j] = gw;
-      db[j] = gb - sinf(arg) * (((s[0] + s[1]) + s[2]) + s[3]);
+      dw[j] = (float)gw;
+      db[j] = (float)(gb - (double)sinf(arg) * (double)(((s[0] + s[1]) + s[2]) + s[3]));
     }
   }
 }

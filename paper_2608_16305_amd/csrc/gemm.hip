@@ -193,21 +193,25 @@ DwPlan dw_batch_plan(int64_t R, const int64_t* N, const int64_t* K, int n) {
 
 namespace {
 
-// Output-stationary batch (k_dw_os): every output at most 112 x 208 with its bias column, both
-// operands at least 4 wide (every DMA instruction of a chunk has an active lane: the waits count them).
+// Output-stationary batch (k_dw_os): every output at most 112 x 208 with its bias column, both operands whole
+// groups of four columns (its loads).
 bool dw_os_shapes_ok(const int64_t* N, const int64_t* K, int n) {
   for (int i = 0; i < n; ++i)
     if (N[i] < 4 || N[i] > 112 || N[i] % 4 != 0 || K[i] < 4 || K[i] % 4 != 0 || K[i] + 1 > 208) return false;
   return true;
 }
 
-// Blocks per problem out of `total`, in proportion to the MFMAs per chunk (7 x 2 or 7 x 4 tiles a wave) times
-// the share of the rows the problem reads (row_den > 0: (row_hi - row_lo) / row_den, else all).
-void dw_os_split(const int64_t* K, int n, int total, int* nblk, const DwProblem* ps = nullptr) {
+// Blocks that R rows' steps of 32 can occupy (more would write partials of zero, which the reduce then reads).
+// 600 rows of 100 by 100, two problems: the launch 15.2 -> 10.7 us.
+int dw_os_useful(int64_t R) { return (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(R, 32), DW_OS_MAX_BLOCKS)); }
+
+// Blocks per problem out of `total`, in proportion to its column groups (two past 111 columns) and the share of
+// the rows that it reads (row_den > 0: (row_hi - row_lo) / row_den, else all of the R).
+void dw_os_split(const int64_t* K, int n, int total, int64_t R, int* nblk, const DwProblem* ps) {
   int w[G_MAXBATCH], sum = 0;
   for (int i = 0; i < n; ++i) {
     w[i] = (cdiv(K[i] + 1, 16) <= 7 ? 2 : 4) * 12;
-    if (ps && ps[i].row_den > 0) w[i] = w[i] * (ps[i].row_hi - ps[i].row_lo) / ps[i].row_den;
+    if (ps[i].row_den > 0) w[i] = w[i] * (ps[i].row_hi - ps[i].row_lo) / ps[i].row_den;
     if (w[i] < 1) w[i] = 1;
     sum += w[i];
   }
@@ -219,6 +223,8 @@ void dw_os_split(const int64_t* K, int n, int total, int* nblk, const DwProblem*
   }
   for (int i = 0; used > total && i < n; ++i)   // only when rounding up single blocks overshot
     while (nblk[i] > 1 && used > total) --nblk[i], --used;
+  for (int i = 0; i < n; ++i)
+    nblk[i] = std::min(nblk[i], dw_os_useful(ps[i].row_den > 0 ? R * (ps[i].row_hi - ps[i].row_lo) / ps[i].row_den : R));
 }
 
 size_t dw_os_ws(const int64_t* N, const int64_t* K, int n, int total) {   // any split of `total` blocks fits
@@ -255,7 +261,7 @@ mtgnn_status linear_dw_batch(const DwProblem* ps, int n, int64_t R, const int32_
   if (os) {   // one block per CU, blocks split over the problems; fixed-order reduce of the partials
     const int total = std::min(dw_os_cu_count(), DW_OS_MAX_BLOCKS);
     int nblk[G_MAXBATCH];
-    dw_os_split(Ks, n, total, nblk, ps);
+    dw_os_split(Ks, n, total, R, nblk, ps);
     DwOsBatch b{};
     ReduceBatch rb{};
     b.n = rb.n = n;
@@ -321,16 +327,15 @@ mtgnn_status linear_dw_batch(const DwProblem* ps, int n, int64_t R, const int32_
   return MTGNN_OK;
 }
 
-// Blocks per tile: the launch's blocks (one per CU, at most DW_OS_MAX_BLOCKS) in proportion to each
-// tile's MFMAs per row chunk (7 x 2 or 7 x 4 tiles a wave), at least one each.
-static int dw_tiles_split(const DwTile* t, int n, int* nblk) {
-  int64_t K[DW_OS_MAXP];
-  for (int i = 0; i < n; ++i) K[i] = t[i].ny;
+// Blocks per tile: the launch's blocks (one per CU, at most DW_OS_MAX_BLOCKS) shared equally (a tile's columns
+// are one group), at least one each and no more than R rows can occupy.
+static int dw_tiles_split(const DwTile* t, int n, int64_t R, int* nblk) {
   const int total = std::max(std::min(dw_os_cu_count(), DW_OS_MAX_BLOCKS), n);
   int w[DW_OS_MAXP], sum = 0;
-  for (int i = 0; i < n; ++i) sum += (w[i] = cdiv(K[i] + 1, 16) <= 7 ? 2 : 4);
+  for (int i = 0; i < n; ++i) sum += (w[i] = cdiv(t[i].ny + 1, 16) <= 7 ? 2 : 4);
   int used = 0;
-  for (int i = 0; i < n; ++i) used += (nblk[i] = std::max(1, (int)((int64_t)total * w[i] / sum)));
+  for (int i = 0; i < n; ++i)
+    used += (nblk[i] = std::min(dw_os_useful(R), std::max(1, (int)((int64_t)total * w[i] / sum))));
   return used;
 }
 
@@ -355,7 +360,7 @@ static bool dw_tiles_ok(const DwTile* t, int n) {
 size_t dw_tiles_ws_bytes(const DwTile* t, int n) {   // depends on the shapes only
   if (!dw_tiles_shapes_ok(t, n)) return 0;
   int nblk[DW_OS_MAXP];
-  dw_tiles_split(t, n, nblk);
+  dw_tiles_split(t, n, INT64_MAX / 2, nblk);   // any R
   size_t b = 0;
   for (int i = 0; i < n; ++i) b += (sizeof(float) * (size_t)nblk[i] * t[i].nx * (t[i].ny + 1) + 255) & ~size_t(255);
   return b;
@@ -367,7 +372,7 @@ mtgnn_status dw_tiles(const DwTile* t, int n, int64_t R, const int32_t* R_dev, v
   if (!dw_tiles_ok(t, n) || dw_os_cu_count() <= 0) return MTGNN_EUNSUPPORTED;
   if (ws_bytes < dw_tiles_ws_bytes(t, n)) return MTGNN_EWORKSPACE;
   int nblk[DW_OS_MAXP];
-  dw_tiles_split(t, n, nblk);
+  dw_tiles_split(t, n, R, nblk);
   DwOsBatch b{};
   ReduceBatch rb{};
   b.n = rb.n = n;

@@ -371,3 +371,26 @@ def test_weight_gradient_of_columns_that_hardly_vary(H, Q):
     err = ((g["W_2"].double() - ref).norm() / ref.norm()).item()
     log(f"  error {err:.2e}")
     assert err <= 1.0e-7
+
+
+def test_time_gradient_sums():
+    """The time encoder's gradient over 60,000 slots whose sine is 1 (arguments of pi / 2): sums of terms of one sign, in
+    64 bits from the blocks' partials on, so the result's own rounding (2.5e-8 on average) is what is left."""
+    dm, dt, da, Q = 4, 64, 128, 60_000
+    rng = np.random.default_rng(9)
+    p = _passing(dm, dt, da)
+    i = torch.arange(dt)
+    p["W_v"][i, dm + i] = 1.0
+    tb = torch.full((dt,), np.float32(np.pi / 2))
+    q_t = torch.from_numpy(rng.uniform(1, 1000, Q).astype(np.float32))
+    dz = torch.zeros(Q, da)
+    dz[:, :dt] = torch.from_numpy((rng.uniform(0.5, 1.0, dt) * (1 + 0.3 * rng.standard_normal((Q, dt))) / Q).astype(np.float32))
+    i32 = dict(dtype=torch.int32)
+    _, g, _ = _forward_backward(p, torch.zeros(2, dm), None, torch.zeros(Q, **i32), q_t, torch.ones(Q, 1, **i32),
+                                torch.zeros(Q, 1), torch.zeros(Q, 1, **i32), torch.zeros(dt), tb, dz, 1, 1,
+                                torch.zeros(1, **i32))
+    d = dz[:, :dt].double()
+    for name, ref in (("time_b", -d.sum(0)), ("time_w", -(d * q_t.double()[:, None]).sum(0))):
+        err = ((g[name].double() - ref) / ref).pow(2).mean().sqrt().item()
+        log(f"[attn] {name} over {Q} slots: error {err:.2e}")
+        assert err <= 3.5e-8, name
