@@ -202,33 +202,36 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
   for (int64_t begin = s0;; begin += NW * DW_SEGMENT) {
     const bool last = begin + NW * DW_SEGMENT >= s1;
     steps(begin, last ? s1 : begin + NW * DW_SEGMENT);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));   // no address of what follows is kept through the steps' loop
+    const int lr = ln & 15, lg = ln >> 4;
 #pragma unroll
     for (int a = 0; a < NI; ++a) {
       float* buf = lds + a % BUFS * 4 * 7 * 256;
 #pragma unroll
-      for (int b = 0; b < NJ; ++b) *(f32x4*)(buf + ((wid * NJ + b) * 64 + lane) * 4) = acc[a][b];
-      if (last) lsum[(a * 4 + wid) * 64 + lane] = cs[a];
+      for (int b = 0; b < NJ; ++b) *(f32x4*)(buf + ((wid * NJ + b) * 64 + ln) * 4) = acc[a][b];
+      if (last) lsum[(a * 4 + wid) * 64 + ln] = cs[a];
       __syncthreads();
       for (int b = mine; b < NJ; b += NW) {
-        f32x4 v = *(const f32x4*)(buf + ((grp * NJ + b) * 64 + lane) * 4);
+        f32x4 v = *(const f32x4*)(buf + ((grp * NJ + b) * 64 + ln) * 4);
 #pragma unroll
-        for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + lane) * 4);
-        f32x4* t = (f32x4*)(total + (((a * G + grp) * NJ + b) * 64 + lane) * 4);   // this lane's alone
+        for (int l = 1; l < NW; ++l) v += *(const f32x4*)(buf + (((grp + G * l) * NJ + b) * 64 + ln) * 4);
+        f32x4* t = (f32x4*)(total + (((a * G + grp) * NJ + b) * 64 + ln) * 4);   // this lane's alone
         if (begin > s0) v += *t;
         if (last) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * fg + r), dw_col<NJ>(b, fr), v[r]);
+          for (int r = 0; r < 4; ++r) store(dw_col<NI>(a, 4 * lg + r), dw_col<NJ>(b, lr), v[r]);
         } else {
           *t = v;
         }
       }
       if (last && wid == 3) {   // the last wave: it has the fewest tiles; group 0's sums
-        float v = lsum[a * 4 * 64 + lane];
+        float v = lsum[a * 4 * 64 + ln];
 #pragma unroll
-        for (int l = 1; l < NW; ++l) v += lsum[(a * 4 + G * l) * 64 + lane];
+        for (int l = 1; l < NW; ++l) v += lsum[(a * 4 + G * l) * 64 + ln];
         v += __shfl_xor(v, 16, 64);
         v += __shfl_xor(v, 32, 64);
-        if (fg == 0) bias(dw_col<NI>(a, fr), v);
+        if (lg == 0) bias(dw_col<NI>(a, lr), v);
       }
       if (BUFS == 1) __syncthreads();
     }
