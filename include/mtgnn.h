@@ -246,17 +246,20 @@ mtgnn_status mtgnn_temporal_attn(const int32_t* q_node, const float* q_t, const 
  * mtgnn_temporal_attn_prepare followed by mtgnn_temporal_attn_prepared on
  * one stream, and the results are bitwise the same.
  *   _prepare  -- from nbr (valid slots lead each row) and the weights, writes
- *                into save the stacked [W_k; W_v] and [b_k; b_v], the padded
- *merge-layer weights (float32), the query projection's constant
+ *                into save copies of the weights (per query: every matrix in
+ *                the matrix instructions' order; per slot: the stacked
+ *                [W_k; W_v] and [b_k; b_v] and, in float32, the padded merge
+ *                layers), the query projection's constant
  *                term b_q + W_q[:, d_mem:] cos(time_b) (every query's time
  *                input is the encoding of 0, so its share is one vector; it
- *                needs time_w and time_b, the forward's) and the per-query
- *                valid-slot counts, their exclusive prefix sums and the
- *                valid total; ws as for mtgnn_temporal_attn.  It is exactly
+ *                needs time_w and time_b, the forward's) and, per slot, the
+ *                per-query valid-slot counts, their exclusive prefix sums and
+ *                the valid total; ws as for mtgnn_temporal_attn.  It is exactly
  *                _prepare_weights (the weight copies and that constant: they
  *                read only the parameters, and their place in save does not
  *                depend on max_q)
- *                followed by _prepare_slots (the counts, offsets and total);
+ *                followed by _prepare_slots (the counts, offsets and total;
+ *                nothing where the attention works per query);
  *                the two may run on different streams, in either order.
  *   _prepared -- the rest of the forward, reading what _prepare wrote into
  *                the same save (same nbr, n_q, max_q, weights and dims); the
@@ -287,7 +290,8 @@ mtgnn_status mtgnn_temporal_attn_prepared(const int32_t* q_node, const float* q_
  *            table is not differentiated across steps;
  *   d_time_w, d_time_b -- [d_time] float32, OVERWRITTEN with the attention's share of the
  *            time-encoder gradient (mtgnn_build_messages_bwd then adds the messages' share).
- * q_node ... neid, memory, edge_feat and save are the forward call's.
+ * q_node, q_t, nbr, nt and save are the forward call's (q_t and nt are read again where the attention
+ * works per query: the slots' time encodings).
  * uniq/n_rows are the rows updated by this step's memory phase (mtgnn_aggregate_last). */
 mtgnn_status mtgnn_temporal_attn_bwd(const int32_t* q_node, const float* q_t, const int32_t* n_q, int64_t max_q,
                                      const int32_t* nbr, const float* nt, const float* dz, const void* save,
@@ -326,8 +330,8 @@ mtgnn_status mtgnn_temporal_attn_bwd_overlap(const int32_t* q_node, const float*
  * queries and the valid neighbour slots, keyed by its updated row, sorted stably by key, and each
  * row's segment bounds, written into ws (the backward's workspace, mtgnn_workspace_bytes for
  * MTGNN_OP_TEMPORAL_ATTN_BWD).  It reads only q_node / n_q, the sampled neighbours nbr
- * [max_q, k], the slot counts and offsets that the attention's preparation left in save, and the
- * updated rows uniq / n_rows, so it may run before the forward's gather and long before any
+ * [max_q, k], the slot counts and offsets that the attention's preparation left in save (where it works
+ * per slot), and the updated rows uniq / n_rows, so it may run before the forward's gather and long before any
  * gradient exists; the caller runs it on the stream it will pass as dmem_stream to
  * mtgnn_temporal_attn_bwd_grouped, which consumes it.  Between the two calls nothing may write
  * ws, save's slot counts, uniq or n_rows.  max_rows == 0: nothing to do.  Errors: EINVAL (a NULL

@@ -996,7 +996,7 @@ struct DwArgs {
 };
 
 __global__ __launch_bounds__(256, 1) void k_proj_dw(DwArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[dw_lds(1)];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   int u = 0;
   while (u + 1 < a.n && (int)blockIdx.x >= a.u[u + 1].b_begin) ++u;
   const DwUnit q = a.u[u];
@@ -1579,9 +1579,13 @@ mtgnn_status proj_params(const int32_t* n_q, int64_t max_q, const float* dz, con
   plan.r.dt2 = 2 * s.dt;
   plan.r.max_q = max_q;
   plan.r.n_q = n_q;
+  int64_t steps = 0;   // of a block, at most
+  for (int i = 0; i < plan.a.n; ++i) steps = std::max(steps, cdiv(cdiv(max_q, 32), plan.a.u[i].nblk));
+  const int lds = dw_lds(1, steps);
+  MTGNN_TRY(lds_limit(k_proj_dw, (size_t)lds));
   {
     TimedScope ts("attn_dw", st);
-    k_proj_dw<<<(unsigned)plan.blocks, 256, 0, st>>>(plan.a);
+    k_proj_dw<<<(unsigned)plan.blocks, 256, lds, st>>>(plan.a);
   }
   MTGNN_CHECK_LAUNCH("proj_dw");
   k_proj_dw_reduce<<<dim3((unsigned)cdiv(plan.maxout, 64), (unsigned)(plan.r.n + 1)), 256, 0, st>>>(plan.r);

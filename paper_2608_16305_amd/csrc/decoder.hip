@@ -9,8 +9,8 @@
 // W_d1 [z_a || z_b] = W_a z_a + W_b z_b with W_a, W_b the two column halves of W_d1, so the first
 // layer is one batched product over all query rows (z W_a^T and z W_b^T); a wave per target event then
 // forms both edges' hidden rows, scores, loss terms and hidden-row gradients.  The gradient rows go to
-// two query-layout buffers, DA (the src rows: dh_pos + dh_neg; zero elsewhere) and DB (dst rows dh_pos,
-// neg rows dh_neg; zero on src rows), so that every remaining product runs over all query rows with
+// two query-layout buffers, DA (the src rows: dh_pos + dh_neg; elsewhere zero, or unwritten and unread with the fused
+// kernel) and DB (dst rows dh_pos, neg rows dh_neg; likewise on src rows), so that every remaining product runs over all query rows with
 // host-known strides: dz = DA W_a + DB W_b, dW_a = DA^T z, dW_b = DB^T z, db_d1 = column sums of DA.
 #include "gemm.h"
 #include "ops.h"

@@ -241,8 +241,13 @@ __device__ __forceinline__ void dw_split(const float* Y, int64_t ldy, int ylim, 
   if (bad != 0.f) again(mine, NW);
 }
 
-// Floats of LDS: buffers, the columns' sums and the totals (G column groups).
-constexpr int dw_lds(int G) { return (G == 2 ? 1 : 2) * 4 * 7 * 256 + 7 * 4 * 64 + G * 7 * 7 * 256; }
+// Bytes of LDS for blocks of at most `steps` steps: buffers, the columns' sums and, past one segment, the totals
+// (G column groups).  Without the totals a block finds room beside another kernel's: the link decoder's gradient beside
+// the attention's backward, 4,000 events, 13 us, with them 29.
+inline int dw_lds(int G, int64_t steps) {
+  const bool totals = steps > 4 / G * DW_SEGMENT;
+  return (int)sizeof(float) * ((totals && G == 2 ? 1 : 2) * 4 * 7 * 256 + 7 * 4 * 64 + (totals ? G * 7 * 7 * 256 : 0));
+}
 
 // The body for the tiles that n by m outputs take (n and m at most 112; m at most 64 with G = 4).
 template <int G, class Out, class Bias>

@@ -528,7 +528,7 @@ constexpr int DW_OS_SHARED = 4;
 template <class Site>   // the call site names the kernel symbol only
 __global__ __launch_bounds__(G_THREADS, 1) void k_dw_os(DwOsBatch b) {
   static_assert(G_THREADS == 256, "four waves");
-  __shared__ __attribute__((aligned(16))) float lds[dw_lds(2)];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const int bx = blockIdx.x;
   int pi = 0;   // the problems' block ranges ascend
 #pragma unroll

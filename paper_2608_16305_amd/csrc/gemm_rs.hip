@@ -1,4 +1,6 @@
 // Host side of the weight-stationary product (gemm_rs.h).
+#include <algorithm>
+
 #include "gemm_rs.h"
 
 namespace mtgnn {
@@ -95,9 +97,23 @@ int dw_os_cu_count() { return cu_count(); }
 
 template <class Site>
 mtgnn_status dw_os_launch(const DwOsBatch& b, int grid, hipStream_t s) {
+  int lds = 0;
+  for (int i = 0; i < b.n; ++i) {
+    const DwOsProblem& q = b.p[i];
+    const int64_t rows = q.row_den > 0 ? b.R * (q.row_hi - q.row_lo) / q.row_den + 1 : b.R;
+    lds = std::max(lds, dw_lds(q.ny <= 112 ? 1 : 2, cdiv(cdiv(rows, 32), q.nblk)));
+  }
+  if (lds > 65536) {   // above what a launch may use without asking
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_dw_os<Site>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) {
+      set_hip_error(e, "dw_os LDS size");
+      return MTGNN_EHIP;
+    }
+  }
   {
     TimedScope ts("dw_os", s);
-    k_dw_os<Site><<<(unsigned)grid, G_THREADS, 0, s>>>(b);
+    k_dw_os<Site><<<(unsigned)grid, G_THREADS, lds, s>>>(b);
   }
   MTGNN_CHECK_LAUNCH("dw_os");
   return MTGNN_OK;

@@ -15,8 +15,9 @@ memory this step's update leaves), and the attention backward's d_mem
 grouping (a key sort), during the embedding; the decoder's first-layer weight
 gradient, during the backward's data gradients; the output and merge layers'
 weight gradients at batches of 65,536 queries or more, beside the score
-backward; and the backward's d_mem sums followed by the GRU backward, during
-the attention parameter gradients.  Results are bitwise those of overlap=False.
+backward (at the widths where the attention works per neighbour slot); and the
+backward's d_mem sums followed by the GRU backward, during the attention
+parameter gradients.  Results are bitwise those of overlap=False.
 """
 
 import numpy as np
@@ -181,8 +182,8 @@ class TGNStep:
         self._gru(lo, hi, save)
 
     def queries(self, lo, hi, stream):
-        """Queries of the batch's target events, their most-recent-k neighbours and the attention's
-        per-query valid-slot counts and offsets: no memory read."""
+        """Queries of the batch's target events, their most-recent-k neighbours and, at the widths where the
+        attention works per neighbour slot, its per-query valid-slot counts and offsets: no memory read."""
         self._q_chain = self._q_chain if self._in_step else 0
         b = self._batch(lo, hi)
         M.mtgnn_build_queries(b, self.neg[lo:hi], self.q_node, self.q_t, self.n_q, self.ws_q, stream=stream)
@@ -192,7 +193,8 @@ class TGNStep:
                                             stream=stream)
 
     def prepare_weights(self, stream, link=False):
-        """The attention's weight copies (stacked K|V, padded merge layers): they read only the weights.
+        """The attention's weight copies (in the matrix instructions' order, or stacked K|V and padded merge
+        layers): they read only the weights.
         link: with the decoder's (same launch), for this step's link loss."""
         self._q_chain = self._q_chain if self._in_step else 0
         p = self.params

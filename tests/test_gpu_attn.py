@@ -88,6 +88,7 @@ CASES = [(1, 4, 4, 0, 4, 1, 5, 5, "f32", False, 10.0),
          (4, 100, 100, 0, 100, 9, 45, 44, "bf16", False, 1e4),
          (4, 100, 100, 16, 100, 10, 3000, 2900, "bf16", False, 1e4),
          (4, 36, 20, 5, 48, 7, 45, 44, "bf16", True, 1e4),
+         (4, 100, 100, 0, 100, 1, 56_000, 55_990, "f32", False, 1e3),   # W_1's 200 columns: two groups, segments
          (2, 100, 100, 260, 100, 20, 45, 44, "f32", False, 1e4),
          (2, 100, 100, 260, 100, 9, 45, 44, "bf16", False, 1e4),
          (1, 96, 100, 260, 100, 20, 45, 44, "f32", False, 1e4),
