@@ -980,6 +980,10 @@ __device__ __forceinline__ void keep_live4(f32x4& v) { asm volatile("" : "+v"(v)
 // one clamped 16-byte group per lane group, unconditionally (a position past the tile's end or past
 // its last key re-reads position 0's row), and the groups outside the row are zeroed afterwards.
 // With no load under a per-lane test, all of a batch's loads are in flight together.
+// TWO: rows past 64 groups.  Without the second group a wave takes 64 registers instead of 104, so that blocks find
+// room beside the weight gradient's (432 of a SIMD's 512): 4,000 events, on the step's second stream, 38 us with it
+// left out, 60 with it (34 beside a gradient of 400 registers).
+template <bool TWO>
 __global__ __launch_bounds__(256) void k_segsum_tiles_v4(SegCtx c) {
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tile = (int64_t)blockIdx.x * 4 + wid;
@@ -999,8 +1003,8 @@ __global__ __launch_bounds__(256) void k_segsum_tiles_v4(SegCtx c) {
   int start = 0;
   f32x4 acc_a = z4, acc_b = z4;
   for (int q0 = 0; q0 < cnt; q0 += SEG_PREFETCH) {
-    f32x4 ra[SEG_PREFETCH], rb[SEG_PREFETCH];
-    bool va[SEG_PREFETCH], vb[SEG_PREFETCH];
+    f32x4 ra[SEG_PREFETCH], rb[TWO ? SEG_PREFETCH : 1];
+    bool va[SEG_PREFETCH], vb[TWO ? SEG_PREFETCH : 1];
 #pragma unroll
     for (int u = 0; u < SEG_PREFETCH; ++u) {
       const int p = q0 + u;
@@ -1013,14 +1017,16 @@ __global__ __launch_bounds__(256) void k_segsum_tiles_v4(SegCtx c) {
                                 : c.dkv + ((int64_t)o - c.max_q) * c.w2 - c.dm;
       const int lo = whole ? 0 : dm4, hi = whole ? dm4 : W4;   // the row's groups: [lo, hi), never empty
       ra[u] = *(const f32x4*)(src + 4 * min(max(qa, lo), hi - 1));
-      rb[u] = *(const f32x4*)(src + 4 * min(max(qb, lo), hi - 1));
       va[u] = live && qa >= lo && qa < hi;
-      vb[u] = live && qb >= lo && qb < hi;
+      if constexpr (TWO) {
+        rb[u] = *(const f32x4*)(src + 4 * min(max(qb, lo), hi - 1));
+        vb[u] = live && qb >= lo && qb < hi;
+      }
     }
 #pragma unroll
     for (int u = 0; u < SEG_PREFETCH; ++u) {
       keep_live4(ra[u]);
-      keep_live4(rb[u]);
+      if constexpr (TWO) keep_live4(rb[u]);
     }
 #pragma unroll
     for (int u = 0; u < SEG_PREFETCH; ++u) {
@@ -1036,11 +1042,15 @@ __global__ __launch_bounds__(256) void k_segsum_tiles_v4(SegCtx c) {
           acc_b = z4;
         }
         acc_a += va[u] ? ra[u] : z4;
-        acc_b += vb[u] ? rb[u] : z4;
+        if constexpr (TWO) acc_b += vb[u] ? rb[u] : z4;
       }
     }
   }
   seg_flush_v4(c, tile, cur, start == 0 && key_before == cur, key_after == cur, qa, qb, acc_a, acc_b);
+}
+void launch_segsum_v4(const SegCtx& c, unsigned blocks, hipStream_t s) {
+  if (c.dm + c.w2 <= 256) k_segsum_tiles_v4<false><<<blocks, 256, 0, s>>>(c);
+  else k_segsum_tiles_v4<true><<<blocks, 256, 0, s>>>(c);
 }
 
 // The rows no tile could finish.  Every wave first zeroes, grid-stride, the rows with no occurrence.
@@ -1415,7 +1425,7 @@ mtgnn_status segsum_rows(const uint32_t* skeys, const uint32_t* svals, int64_t n
     MTGNN_CHECK_LAUNCH("seg_bounds");
     const unsigned gt = (unsigned)cdiv(ntiles, 4);
     if (dm % 4 == 0 && ld % 4 == 0 && ((uintptr_t)src | (uintptr_t)D) % 16 == 0) {
-      k_segsum_tiles_v4<<<gt, 256, 0, s>>>(c);
+      launch_segsum_v4(c, gt, s);
     } else {
       switch (cdiv(dm, 64)) {
         case 1: k_segsum_tiles<1><<<gt, 256, 0, s>>>(c); break;
@@ -1633,7 +1643,7 @@ mtgnn_status attn_bwd_dmem_sum(int64_t max_q, bool proj, const AttnShape& sh, co
     const int64_t ntiles = cdiv(n_occ, SEG_TILE);
     const unsigned gt = (unsigned)cdiv(ntiles, 4);
     if (dm % 4 == 0 && da % 4 == 0 && dm + 2 * da <= 512 && ((uintptr_t)d_mem & 15) == 0) {   // 16-byte groups
-      k_segsum_tiles_v4<<<gt, 256, 0, s>>>(c);
+      launch_segsum_v4(c, gt, s);
     } else {
       switch (cdiv(dm + c.w2, 64)) {   // column chunks per lane (validation keeps the width <= 512)
         case 1: k_segsum_tiles<1><<<gt, 256, 0, s>>>(c); break;
