@@ -10,8 +10,8 @@
 //
 // Measured against a key/value product over every slot (its rows gathered to memory, the softmax and its
 // backward in kernels of their own), 60,000 events, 20 slots, width 100, 16 edge features, 2 heads:
-// forward 3340 -> 1256 us, backward 4710 -> 2058 us; bfloat16, no edge features, both: 6290 -> 2378 us; 4,000
-// events, 10 slots: backward 321 -> 213 us; 600 events, 172 edge features: forward 93 -> 57 us.
+// forward 3340 -> 1255 us, backward 4710 -> 2109 us; bfloat16, no edge features, both: 6290 -> 2526 us; 4,000
+// events, 10 slots: backward 321 -> 210 us; 600 events, 172 edge features: forward 93 -> 59 us.
 #include <algorithm>
 #include <cfloat>
 
@@ -1300,7 +1300,11 @@ size_t fwd_lds(const ProjShape& s, int rows) { return sizeof(float) * (size_t)ro
 size_t bwd_lds(const ProjShape& s) { return sizeof(float) * 16 * (size_t)(s.us + s.uu + 2 * s.as); }
 
 // Blocks of 32 queries (half the weight reads per query) from this many query rows on, where they still
-// fill the chip; of 16 below.
+// fill the chip; of 16 below.  Blocks of 16 and of 32, us: width 100, 16 edge features, 10 slots: 4,500 queries 61
+// and 69, 9,000 91 and 99, 15,000 114 and 99, 24,000 163 and 148, 120,000 753 and 665; bfloat16 58 and 74, 89 and
+// 98, 110 and 102, 158 and 150, 709 and 632.  They cross between 9,000 and 15,000 (width 64, 100 edge features: near
+// 9,000 in float32, near 24,000 in bfloat16); up to the line some thousand rows run 5 to 17 % over the other's time.
+// fwd_lds <= 81920: two blocks a CU fit.
 constexpr int64_t FWD_RT2_ROWS = 16384;
 
 template <typename K>

@@ -79,7 +79,8 @@ __device__ __forceinline__ float dw_plain(const float* y, int64_t ldy, const flo
 // An operand past the largest bfloat16, or infinite, meets the others' zero parts (NaN): a lane that stores a sum
 // which is not finite goes over its sums again with float32 products.
 // Matrix time and the operands' reads bound it about equally.  Against 16x16x4 float32 instructions: the
-// attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us, of 12,000 rows 46 -> 34 us.
+// attention's eight products of 180,000 rows (1.35 GB) 500 -> 352 us (before the segments
+// below, which add 55), of 12,000 rows 46 -> 35 us.
 //
 // An instruction rounds its accumulator every eight products (16x16x4: every one), so a long sum's error is of those
 // roundings at its full size: a sum of DW_SEGMENT steps joins the total by one addition.  The attention's value
